@@ -101,7 +101,10 @@ typedef struct {
 } sweep_problem;
 
 /* Tile / launch choices (what the autotuner searches). Results are bitwise
- * independent of every field here. */
+ * independent of every field here. With the default tiling of an acoustic plan
+ * (rz 8, pml_rz 4, tblock 2) a call over few cells takes one launch per step
+ * for the whole grid in place of one per tile set; any other tiling is taken
+ * as it is named. */
 typedef struct {
   int rz;          /* acoustic tiles are 64 x 4 rz cells; rows per thread of the
                       interior kernel: 1, 2, 4 or 8 (default 8) */
@@ -283,7 +286,8 @@ int sweep_backward(sweep_plan* plan, const float* d_resid, float* d_grad, void* 
  * B^n (6-8): interior-tile kernel, z-frame C-PML kernel, x-frame C-PML kernel;
  * with tuning.tblock = 2 the two-step passes over the deep tiles are classes 9
  * (forward), 10 (adjoint) and 11 (recompute), and the interior classes then
- * time the remaining interior tiles. An elastic plan times each whole step
+ * time the remaining interior tiles. Steps that take one launch for the whole
+ * grid are timed as x-frame launches. An elastic plan times each whole step
  * (both of its kernels) in classes 0, 3 and 6.
  * enable: 0 off; n >= 1 times the launches of every n-th step (n = 1: all); a
  * step pair of a two-step pass counts as three launch groups (deep pass, step

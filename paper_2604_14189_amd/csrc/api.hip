@@ -285,6 +285,24 @@ int check_work(const sweep_plan* p, size_t need, void* work, size_t bytes) {
   return SWEEP_OK;
 }
 
+size_t ac_cells(const sweep_plan* p) { return (size_t)p->pb.nshots * p->NX * p->NZ; }
+
+// Whether the steps of a call over `cells` padded cells (all shots) take one
+// launch for the whole grid; `adjoint`: the call has adjoint or Born steps.
+// Only under the default tiling, so that a tiling that the caller names is the
+// one that runs. One launch wins while launches and latency bound a step, and
+// beyond that while the fields stay in the 256 MB last-level cache: they take
+// 16 bytes a cell forward and up to 28 with the adjoint's operands. us per step
+// by tile sets / in one launch (1080 x 380 shots): forward 1 shot 21.3 / 6.3,
+// 16 shots (6.6 M cells) 37.2 / 29.9, 32 shots (13.1 M) 61.6 / 54.1, 64 shots
+// (26 M) 107.7 / 146.4; gradient 1 shot 70.9 / 21.7, 16 shots 140.3 / 114.2, 32
+// shots 238.2 / 239.4; Born 16 shots 87.5 / 69.7, 32 shots 153.0 / 159.8.
+constexpr size_t kWholeForward = 13600000, kWholeAdjoint = 8400000;
+bool ac_whole(const sweep_tuning& t, size_t cells, bool adjoint) {
+  return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2 &&
+         cells <= (adjoint ? kWholeAdjoint : kWholeForward);
+}
+
 AcStep ac_base(const sweep_plan* p, void* work, const AcLayout& L) {
   AcStep a;
   std::memset(&a, 0, sizeof(a));
@@ -296,8 +314,8 @@ AcStep ac_base(const sweep_plan* p, void* work, const AcLayout& L) {
   a.nshots = p->pb.nshots;
   a.tiles_x = p->tiles_x;
   a.ntiles = p->ntiles;
-  // encoded shots: the step kernels inject nothing (ac_encode_sources does)
-  a.w = p->nsrc > 1 ? 0.0f : (float)((double)p->pb.dt * p->pb.dt / ((double)p->pb.h * p->pb.h));
+  // encoded shots: the kernels by tile set inject nothing (ac_encode_sources does)
+  a.w = p->nsrc > 1 && !p->whole ? 0.0f : (float)((double)p->pb.dt * p->pb.dt / ((double)p->pb.h * p->pb.h));
   a.Cs = at<float>(work, L.Cs);
   a.ax = at<float>(work, L.ax);
   a.bx = at<float>(work, L.bx);
@@ -319,6 +337,7 @@ AcStep ac_base(const sweep_plan* p, void* work, const AcLayout& L) {
   a.n_zf = p->n_zf;
   a.tz = p->TZ;
   a.nsub = p->tune.rz / p->tune.pml_rz;
+  a.nsrc = p->nsrc;
   return a;
 }
 
@@ -404,6 +423,7 @@ AcStep ac_fwd_single(sweep_plan* p, void* work, const AcLayout& L, int n, int pa
 // Timer events for the launches of one step; a tile set with nothing to launch
 // gets no events (they would never be recorded).
 hipEvent_t* step_events(sweep_plan* p, const AcStep& a, int ci, int cz, int cx) {
+  if (p->whole) return p->timer.take(-1, -1, cx);
   return p->timer.take(a.n_int > 0 ? ci : -1, a.n_zf > 0 ? cz : -1, a.n_xf > 0 ? cx : -1);
 }
 
@@ -411,7 +431,7 @@ hipEvent_t* step_events(sweep_plan* p, const AcStep& a, int ci, int cz, int cx) 
 // on source cells recorded again; nothing for one source per shot.
 int ac_encode_sources(sweep_plan* p, void* work, const AcLayout& L, int n, float* next,
                       float* gathers, hipStream_t s) {
-  if (p->nsrc <= 1) return SWEEP_OK;
+  if (p->nsrc <= 1 || p->whole) return SWEEP_OK;
   const sweep_problem& pb = p->pb;
   const float w = (float)((double)pb.dt * pb.dt / ((double)pb.h * pb.h));
   return ac_launch_inject_encoded(next, L.plane, at<int>(work, L.src_cell),
@@ -420,13 +440,28 @@ int ac_encode_sources(sweep_plan* p, void* work, const AcLayout& L, int n, float
                                   at<int>(work, L.rec_cell), gathers, pb.nrec, s);
 }
 
+// The launches of one step: the whole grid in one (timed as the x frame, which
+// is the kernel's general case), or one for each tile set.
+int ac_step(const sweep_plan* p, const AcStep& a, GridStep kind, hipStream_t s, hipEvent_t* ev) {
+  const int rz = p->tune.rz, prz = p->tune.pml_rz;
+  if (!p->whole)
+    return kind == kGridAdj   ? ac_launch_adj(a, rz, prz, s, ev)
+           : kind == kGridFwd ? ac_launch_fwd(a, rz, prz, s, ev)
+                              : ac_launch_born(a, rz, prz, s);
+  if (ev && ev[4]) SWEEP_HIP(hipEventRecord(ev[4], s));
+  const int rc = ac_launch_grid(a, kind, s);
+  if (rc) return rc;
+  if (ev && ev[5]) SWEEP_HIP(hipEventRecord(ev[5], s));
+  return SWEEP_OK;
+}
+
 // One forward-type step from the plan's rotation; advances it.
 int ac_fwd_one(sweep_plan* p, void* work, const AcLayout& L, int n, int par, float* gathers,
                float* B_out, hipStream_t s, int ci, int cz, int cx) {
   Rot& r = p->frot;
   const int o = r.free_buf(0);
   const AcStep a = ac_fwd_single(p, work, L, n, par, r.cur, r.prev, o, gathers, B_out);
-  int rc = ac_launch_fwd(a, p->tune.rz, p->tune.pml_rz, s, step_events(p, a, ci, cz, cx));
+  int rc = ac_step(p, a, kGridFwd, s, step_events(p, a, ci, cz, cx));
   if (!rc) rc = ac_encode_sources(p, work, L, n, a.next, gathers, s);
   r.prev = r.cur;
   r.cur = o;
@@ -474,7 +509,9 @@ int ac_fwd_two(sweep_plan* p, void* work, const AcLayout& L, int n, int par, flo
   return ac_encode_sources(p, work, L, n + 1, P.a1.next, gathers, s);
 }
 
-bool ac_two_steps(const sweep_plan* p) { return p->tune.tblock == 2 && !p->dlist.empty(); }
+bool ac_two_steps(const sweep_plan* p) {
+  return p->tune.tblock == 2 && !p->dlist.empty() && !p->whole;
+}
 
 void ac_mark_saved(sweep_plan* p, void* work, const float* model, int save) {
   p->saved = save != 0;
@@ -580,7 +617,7 @@ int ac_adj_one(sweep_plan* p, void* work, const AcLayout& L, const float* resid,
   Rot& r = p->arot;
   const int o = r.free_buf(0);
   const AcStep a = ac_adj_single(p, work, L, resid, n, n0, n1, r.cur, r.prev, o);
-  const int rc = ac_launch_adj(a, p->tune.rz, p->tune.pml_rz, s, step_events(p, a, kAdjInt, kAdjZ, kAdjX));
+  const int rc = ac_step(p, a, kGridAdj, s, step_events(p, a, kAdjInt, kAdjZ, kAdjX));
   r.prev = r.cur;
   r.cur = o;
   return rc;
@@ -717,6 +754,7 @@ int ac_forward(sweep_plan* p, const float* model, const float* wavelet, float* g
   int rc = check_work(p, save ? L.bwd_end : L.fwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
+  p->whole = ac_whole(p->tune, ac_cells(p), false);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {model, wavelet, gathers, work, (const void*)(size_t)save};
   rc = run_maybe_graph(p->gfwd, graph, key, s, [&](hipStream_t st) {
@@ -742,6 +780,7 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
+  p->whole = ac_whole(p->tune, ac_cells(p), true);
   if ((rc = ac_fwd_prologue(p, model, wavelet, work, L, s))) return rc;
   const sweep_problem& pb = p->pb;
   const size_t ns = pb.nshots;
@@ -755,7 +794,6 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   float* daux[2] = {at<float>(work, L.adjaux[0]), at<float>(work, L.adjaux[1])};
   if ((rc = launch_fill(daux[0], L.aux_elems, 0.0f, s))) return rc;
   if ((rc = launch_fill(daux[1], L.aux_elems, 0.0f, s))) return rc;
-  const int rz = p->tune.rz, prz = p->tune.pml_rz;
   // perturbation step n with the background's B'^n in B
   auto dstep = [&](int n, const float* B) {
     const int par = n % 2;
@@ -771,7 +809,7 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
     set_aux(d, aux_ptrs(daux[par], L, ns), aux_ptrs(daux[1 - par], L, ns));
     d.bdC = dCs;
     d.bB = B;
-    const int r = ac_launch_born(d, rz, prz, s);
+    const int r = ac_step(p, d, kGridBorn, s, nullptr);
     br.prev = br.cur;
     br.cur = o;
     return r;
@@ -808,6 +846,7 @@ int ac_backward(sweep_plan* p, const float* resid, float* grad, void* work, size
   ac_layout(p, L);
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
+  p->whole = ac_whole(p->tune, ac_cells(p), true);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {resid, grad, work};
   return run_maybe_graph(p->gbwd, graph, key, s, [&](hipStream_t st) {
@@ -872,6 +911,21 @@ AcStep adj_single_rot(sweep_plan* p, void* work, const AcLayout& L, const float*
   return a;
 }
 
+// As for one plan, by the cells of all plans of the batch.
+void batch_set_whole(sweep_batch* b, bool adjoint) {
+  size_t cells = 0;
+  for (const sweep_plan* p : b->plans) cells += ac_cells(p);
+  b->whole = true;
+  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_whole(p->tune, cells, adjoint);
+  for (sweep_plan* p : b->plans) p->whole = b->whole;
+}
+int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep kind,
+               hipStream_t s) {
+  const int n = (int)steps.size();
+  if (b->whole) return ac_launch_grid_batch(steps.data(), n, kind, s);
+  return kind == kGridAdj ? ac_launch_adj_batch(steps.data(), n, b->rz, b->prz, s)
+                          : ac_launch_fwd_batch(steps.data(), n, b->rz, b->prz, s);
+}
 // nmax: stop after that many steps (the autotuner's short runs).
 int batch_forward_enqueue(sweep_batch* b, const float* const* models, const float* const* wavs,
                           float* const* gathers, void* work, const std::vector<AcLayout>& L,
@@ -879,6 +933,7 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
                           int nmax = INT_MAX) {
   const int np = (int)b->plans.size();
   int rc, maxnt = 0;
+  batch_set_whole(b, false);
   for (int q = 0; q < np; ++q) {
     if ((rc = ac_fwd_prologue(b->plans[q], models[q], wavs[q], at<char>(work, off[q]), L[q], s)))
       return rc;
@@ -909,7 +964,7 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
       }
     }
     if ((rc = ac_launch_deep_batch(B.deep.data(), (int)B.deep.size(), false, s))) return rc;
-    if ((rc = ac_launch_fwd_batch(B.s0.data(), (int)B.s0.size(), b->rz, b->prz, s))) return rc;
+    if ((rc = batch_step(b, B.s0, kGridFwd, s))) return rc;
     for (int q : B.later) {
       sweep_plan* p = b->plans[q];
       void* wq = at<char>(work, off[q]);
@@ -921,9 +976,7 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
       B.s1.push_back(fwd_single_rot(p, wq, L[q], n + 1, (n + 1) % 2, gathers[q],
                                     keepB ? ac_bseg(p, wq, L[q], sg, m) : nullptr));
     }
-    if (!B.s1.empty() &&
-        (rc = ac_launch_fwd_batch(B.s1.data(), (int)B.s1.size(), b->rz, b->prz, s)))
-      return rc;
+    if (!B.s1.empty() && (rc = batch_step(b, B.s1, kGridFwd, s))) return rc;
   }
   return SWEEP_OK;
 }
@@ -937,6 +990,7 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
   const int np = (int)b->plans.size();
   int rc;
   BatchPair B;
+  batch_set_whole(b, true);
   // recompute the segments, storing B^n (not those the saving forward stored)
   for (int m = 0; m < lenmax; m += 2) {
     B.clear();
@@ -957,16 +1011,14 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
       }
     }
     if ((rc = ac_launch_deep_batch(B.deep.data(), (int)B.deep.size(), false, s))) return rc;
-    if ((rc = ac_launch_fwd_batch(B.s0.data(), (int)B.s0.size(), b->rz, b->prz, s))) return rc;
+    if ((rc = batch_step(b, B.s0, kGridFwd, s))) return rc;
     for (int q : B.later) {
       sweep_plan* p = b->plans[q];
       void* wq = at<char>(work, off[q]);
       B.s1.push_back(fwd_single_rot(p, wq, L[q], n0[q] + m + 1, (m + 1) % 2, nullptr,
                                     ac_bseg(p, wq, L[q], n0[q] / p->ckpt, m + 1)));
     }
-    if (!B.s1.empty() &&
-        (rc = ac_launch_fwd_batch(B.s1.data(), (int)B.s1.size(), b->rz, b->prz, s)))
-      return rc;
+    if (!B.s1.empty() && (rc = batch_step(b, B.s1, kGridFwd, s))) return rc;
   }
   // reverse steps n1-1 .. n0
   for (int m = 0; m < lenmax; m += 2) {
@@ -985,15 +1037,13 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
       }
     }
     if ((rc = ac_launch_deep_batch(B.deep.data(), (int)B.deep.size(), true, s))) return rc;
-    if ((rc = ac_launch_adj_batch(B.s0.data(), (int)B.s0.size(), b->rz, b->prz, s))) return rc;
+    if ((rc = batch_step(b, B.s0, kGridAdj, s))) return rc;
     for (int q : B.later) {
       sweep_plan* p = b->plans[q];
       B.s1.push_back(adj_single_rot(p, at<char>(work, off[q]), L[q], resids[q],
                                     n1[q] - 2 - m, n0[q], n1[q]));
     }
-    if (!B.s1.empty() &&
-        (rc = ac_launch_adj_batch(B.s1.data(), (int)B.s1.size(), b->rz, b->prz, s)))
-      return rc;
+    if (!B.s1.empty() && (rc = batch_step(b, B.s1, kGridAdj, s))) return rc;
   }
   return SWEEP_OK;
 }
@@ -1757,7 +1807,9 @@ extern "C" int sweep_plan_autotune(sweep_plan* p, const float* d_model, const fl
       p->tune.pml_rz = cp;
       p->tune.tblock = tb;
       ac_build_tiling(p);
-      if (tb == 2 && !ac_two_steps(p)) continue;  // no deep tiles: same as tb = 1
+      p->whole = ac_whole(p->tune, ac_cells(p), false);
+      // no deep tiles: same as tb = 1
+      if (tb == 2 && !p->whole && !ac_two_steps(p)) continue;
       if ((rc = ac_upload_geometry(p, d_work, L, s))) break;
       for (int rep = 0; rep < 2 && !rc; ++rep) {  // first pass warms up
         rc = ac_fwd_prologue(p, d_model, d_wavelet, d_work, L, s);
@@ -1893,7 +1945,8 @@ extern "C" int sweep_batch_autotune(sweep_batch* b, const float* const* d_models
       for (int tb = 1; tb <= 2 && !rc; ++tb) {
         if (cp > c) continue;
         if ((rc = apply(c, cp, tb))) break;
-        bool deep = false;
+        batch_set_whole(b, false);
+        bool deep = b->whole;
         for (sweep_plan* p : b->plans) deep = deep || ac_two_steps(p);
         if (tb == 2 && !deep) continue;  // no deep tiles: the same as tblock = 1
         for (int q = 0; q < np && !rc; ++q)

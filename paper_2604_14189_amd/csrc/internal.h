@@ -177,6 +177,7 @@ struct AcStep {
   int n_xf, n_zf;  // frame tiles: left/right columns (x frame), above/below (z frame)
   int tz;    // rows of a tile
   int nsub;  // PML work-groups per frame tile (each takes tz / nsub rows)
+  int nsrc;  // sources per shot (one-launch steps; the other kernels take one)
   // Born (tangent-linear) step, Eq. 16: p^{n+1} += dCs * bB at every cell
   // (last, so the other fields keep their kernel-argument offsets)
   const float* bdC;       // [NZ][NX] dCs = 2 v dv (dt/h)^2
@@ -222,6 +223,11 @@ int ac_launch_inject_encoded(float* next, size_t plane, const int* src_cell, con
                              hipStream_t s);
 int ac_launch_born_prep(const float* v, const float* dv, float* dCs, int nx, int nz, int P,
                         double h, double dt, hipStream_t s);
+// One step of the whole grid in one launch, whatever the tile sets
+// (acoustic_grid.hip); a.tz must be a multiple of 8. A batch has no Born steps.
+enum GridStep { kGridFwd, kGridAdj, kGridBorn };
+int ac_launch_grid(const AcStep& a, GridStep kind, hipStream_t s);
+int ac_launch_grid_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s);
 int ac_launch_fwd_batch(const AcStep* steps, int n, int rz, int prz, hipStream_t s);
 // Two steps over the deep runs (a.drun): forward n and n+1, or adjoint n and n-1.
 int ac_launch_deep(const AcStep& a, bool adj, hipStream_t s, hipEvent_t* ev);

@@ -154,6 +154,9 @@ struct sweep_plan {
   // interior tiles; those advanced two steps per pass (deep) and the others
   std::vector<int> ilist_all, ilist_ring, dlist;
   std::vector<int2> drun;  // deep tiles as chunks of tile-column runs
+  // steps take one launch for the whole grid (set by every call, for the plan
+  // alone or for the batch it runs in)
+  bool whole = false;
   sweep::Rot frot, arot;  // forward / adjoint buffer rotation
   // elastic: receivers sorted by (shot, cell, r) for deterministic injection,
   // and the transposed z-taps of the first rows under a free surface
@@ -218,6 +221,7 @@ struct sweep_batch {
   int device = -1;                 // the plans' device (-1: current at each call)
   int rz = 8, prz = 2;
   bool use_graph = false;
+  bool whole = false;  // as sweep_plan::whole, for all plans (set by every call)
   bool saved = false;
   const void* saved_work = nullptr;
   std::vector<unsigned> saved_gen;  // the plans' tuning generations at the saving forward
