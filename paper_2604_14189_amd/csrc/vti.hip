@@ -14,6 +14,7 @@
 // each lane finishes its four cells from LDS. P^{n+1} and G^{n+1} overwrite
 // P^{n-1} and G^{n-1} at the lane's own cells (each is read there only).
 #include "fd.h"
+#include "finish.h"
 #include "internal.h"
 #include "vti.h"
 
@@ -735,26 +736,34 @@ __global__ void vti_fold_kernel(double* tot, const float* __restrict__ gpart, in
 // dJ/d(vv, v, eta) of model cell (ii, jj): the chain rule through (cx, cz, cm),
 // summed over the padded cells that replicate the cell (vv and v); eta only at
 // the cell itself (the pad holds eta = 0, which depends on no model value).
-__global__ void vti_finish_kernel(const double* tot, const float* pad, float* grad, int nx,
-                                  int nz, int P, double r) {
-  const int ii = blockIdx.x * blockDim.x + threadIdx.x;
-  const int jj = blockIdx.y;
-  if (ii >= nx || jj >= nz) return;
+// The border takes a wave per cell, as in the acoustic kernel
+// (1080 x 380 cells, P = 40: 325 us with a thread per cell, now 21 us).
+__global__ __launch_bounds__(256) void vti_finish_kernel(const double* tot, const float* pad,
+                                                         float* grad, int nx, int nz, int P,
+                                                         double r) {
+  int ii, jj, lane, nl;
+  if (!finish_cell(nx, nz, ii, jj, lane, nl)) return;
   const int NX = nx + 2 * P, NZ = nz + 2 * P;
   const size_t plane = (size_t)NX * NZ, mn = (size_t)nx * nz;
   const int i0 = ii == 0 ? 0 : ii + P, i1 = ii == nx - 1 ? NX - 1 : ii + P;
   const int j0 = jj == 0 ? 0 : jj + P, j1 = jj == nz - 1 ? NZ - 1 : jj + P;
+  const int w = i1 - i0 + 1, n = w * (j1 - j0 + 1);
   const double r2 = r * r, r4 = r2 * r2;
   double gvv = 0.0, gvn = 0.0, geta = 0.0;
-  for (int j = j0; j <= j1; ++j)
-    for (int i = i0; i <= i1; ++i) {
-      const size_t c = (size_t)j * NX + i;
-      const double vv = pad[c], vn = pad[plane + c], eta = pad[2 * plane + c];
-      const double gx = tot[c], gz = tot[plane + c], gm = tot[2 * plane + c];
-      gvv += gz * 2.0 * vv * r2 + gm * 4.0 * eta * vn * vn * vv * r4;
-      gvn += gx * 2.0 * (1.0 + 2.0 * eta) * vn * r2 + gm * 4.0 * eta * vn * vv * vv * r4;
-      if (i == ii + P && j == jj + P) geta += gx * 2.0 * vn * vn * r2 + gm * 2.0 * vn * vn * vv * vv * r4;
-    }
+  for (int t = lane; t < n; t += nl) {
+    const int j = j0 + t / w, i = i0 + t % w;
+    const size_t c = (size_t)j * NX + i;
+    const double vv = pad[c], vn = pad[plane + c], eta = pad[2 * plane + c];
+    const double gx = tot[c], gz = tot[plane + c], gm = tot[2 * plane + c];
+    gvv += gz * 2.0 * vv * r2 + gm * 4.0 * eta * vn * vn * vv * r4;
+    gvn += gx * 2.0 * (1.0 + 2.0 * eta) * vn * r2 + gm * 4.0 * eta * vn * vv * vv * r4;
+    if (i == ii + P && j == jj + P)
+      geta += gx * 2.0 * vn * vn * r2 + gm * 2.0 * vn * vn * vv * vv * r4;
+  }
+  gvv = finish_sum(gvv, nl);
+  gvn = finish_sum(gvn, nl);
+  geta = finish_sum(geta, nl);
+  if (lane) return;
   const size_t m = (size_t)jj * nx + ii;
   grad[m] = (float)gvv;
   grad[mn + m] = (float)gvn;
@@ -806,7 +815,7 @@ int vti_launch_fold(double* tot, const float* gpart, int nshots, size_t plane, h
 
 int vti_launch_finish(const double* tot, const float* pad, float* grad, int nx, int nz, int P,
                       double r, hipStream_t s) {
-  hipLaunchKernelGGL(vti_finish_kernel, dim3((nx + 255) / 256, nz), dim3(256), 0, s, tot, pad, grad,
+  hipLaunchKernelGGL(vti_finish_kernel, finish_grid(nx, nz), dim3(256), 0, s, tot, pad, grad,
                      nx, nz, P, r);
   SWEEP_HIP(hipGetLastError());
   return SWEEP_OK;
