@@ -1191,14 +1191,7 @@ extern "C" int sweep_plan_create(const sweep_ctx* ctx, const sweep_problem* pb,
     ac_build_tiling(p);
   } else {
     el_build_tables(p);
-    p->rec_sorted.resize(p->rec_cell.size());
-    for (size_t r = 0; r < p->rec_cell.size(); ++r)
-      p->rec_sorted[r] = make_int4((int)(r / pb->nrec), p->rec_cell[r], (int)(r % pb->nrec), 0);
-    std::sort(p->rec_sorted.begin(), p->rec_sorted.end(), [](const int4& a, const int4& b) {
-      if (a.x != b.x) return a.x < b.x;
-      if (a.y != b.y) return a.y < b.y;
-      return a.z < b.z;
-    });
+    el_build_receivers(p);
   }
   *out = p;
   return SWEEP_OK;

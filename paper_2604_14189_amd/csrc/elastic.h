@@ -5,6 +5,8 @@
 
 namespace sweep {
 
+constexpr int kElTileRows = 16;  // rows of a tile of the step kernels
+
 // Shared (per plan) coefficient arrays on the padded grid.
 struct ElCoef {
   float *vp, *vs, *rho, *lam, *mu;              // [NZ][NX]
@@ -20,6 +22,7 @@ struct ElCoef {
 // One time step (forward) or its reverse (adjoint) for all shots of a plan.
 struct ElStep {
   int NX, NZ, nt, nrec, nshots, n, fs;
+  int P, top;       // pad cells left, right and below, and above (0 under a free surface)
   int fluid;        // vs = 0 (first-order acoustic): the kernels' fluid variants
   float dt, w, ih;  // time step, source scale dt/h^2, 1/h
   const float *bx, *bz, *mxz, *cxx_x, *cxx_z, *smask, *dM_dl, *dM_dm;
@@ -36,7 +39,10 @@ struct ElStep {
   const int* src_cell;
   const float* wavelet;
   const int* rec_cell;    // [nshots][nrec]
-  const int4* rec_sorted; // (shot, cell, r, 0) sorted
+  // (shot, cell, r, -) sorted; with rec_dir, the fourth word of a shot's entry k is
+  // its first entry in row k of the 16-row tiles or below (k up to the row count)
+  const int4* rec_sorted;
+  int rec_dir;
   float* gathers;         // [nshots][nt][nrec][2]
   const float* resid;
   // transposed z-taps of the first four rows under a free surface, per kind:

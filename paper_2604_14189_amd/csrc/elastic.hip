@@ -13,8 +13,8 @@
 // variable psi <- b psi + a D f, stored over the whole grid but touched only
 // where a != 0.
 //
-// Forward step: velocity kernel (vx, vz), receiver gather, stress kernel
-// (txx, tzz, txz, explosive source). Every step kernel has a fluid variant
+// Forward step: velocity kernel (vx, vz), stress kernel (txx, tzz, txz,
+// explosive source; it also gathers the receivers). Every step kernel has a fluid variant
 // (kFluid, the first-order acoustic system at vs = 0): there mu = 0, so txz
 // stays 0, and the shear stress, its four memory variables and the mu
 // partials of the adjoint enter only through products with 0. The variant
@@ -22,7 +22,7 @@
 // the elastic kernels' results at vs = 0 while moving about a fifth fewer
 // bytes forward and a quarter fewer in reverse. Reverse step (gather form of the
 // transpose): adjoint-stress kernel (updates the velocity adjoints from the
-// stress adjoints), residual injection, adjoint-velocity kernel. Away from the
+// stress adjoints and injects the residuals), adjoint-velocity kernel. Away from the
 // surface the transposes are (Dx+)^T = -Dx-, (Dx-)^T = -Dx+ (and along z); on the
 // first four rows below a free surface they use tap tables derived on the host
 // from the forward taps.
@@ -36,310 +36,498 @@ constexpr float C1 = 9.0f / 8.0f;
 constexpr float C2 = -1.0f / 24.0f;
 
 // ---------------------------------------------------------------------------
-// Tiles: 64 columns x kElTZ rows per work-group, thread (lx, w) owns column lx
-// and rows [w kElRZ, w kElRZ + kElRZ). The fields (or derived quantities) a
-// kernel differentiates are staged in LDS on the tile plus a 2-cell halo, zero
-// outside the grid, so the stencils read LDS and every global load is
-// coalesced and issued once per tile.
+// Tiles: 64 columns x 16 rows per work-group; thread t owns the four columns
+// 4 (t & 15) .. + 3 of row t / 16, so a field is one 16-byte access a thread and
+// a wave covers four rows. What a kernel differentiates is staged in LDS, zero
+// outside the grid: every thread stages its own cells (and keeps them in
+// registers), one wave the two rows above and below the tile and another the two
+// columns left and right of it. Which waves these are rotates with the
+// work-group, so that no SIMD takes all the halos. A plane that is differentiated
+// along one axis only has the halo of that axis only.
+//
+// The steps move 7 to 16 planes per cell and are bound by memory. Forward they
+// run near a stream of the same planes; in reverse a work-group's chain (loads,
+// LDS, update) leaves part of the bandwidth idle. 16-byte items instead of one
+// column a thread halve the memory instructions and the address arithmetic. The
+// fields of up to about 200 MB of shots stay in the last-level cache from kernel
+// to kernel, so what is used once a step (traces, gradient partials) passes by it
+// with the non-temporal hint: on 680 x 380 cells and 32 shots the traced stress
+// step takes 56 us with the hint on the traces and 92 us without, the reverse
+// stress step 117 us with it on traces and partials and 135 us without. On the
+// fields themselves the hint costs 10 to 30 %.
+// us a launch on 660 x 330 cells, 32 shots, mean over a gradient that stores half
+// of its segments, with one column a thread and no hints -> now: velocity 55 ->
+// 43, stress 66 -> 52, reverse stress 136 -> 102, reverse velocity 112 -> 82.
 // ---------------------------------------------------------------------------
-constexpr int kElRZ = 4;
-constexpr int kElTZ = 4 * kElRZ;
-constexpr int kElBW = kTX + 4;
-constexpr int kElBH = kElTZ + 4;
-constexpr int kElBox = kElBW * kElBH;
-constexpr int kElK = (kElBox + kThreads - 1) / kThreads;
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+// rows start at any 4-byte address when NX is odd
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr f2 kZ2 = {0.0f, 0.0f};
+constexpr f4 kZ4 = {0.0f, 0.0f, 0.0f, 0.0f};
+constexpr int kElTZ = kElTileRows;
+constexpr int kElXP = kTX + 8;     // row pitch of a plane with an x halo: column c at 4 + c
+constexpr int kElZH = kElTZ + 4;   // rows of a plane with a z halo: row r at 2 + r
+static_assert(kThreads == kElTZ * kTX / 4, "four cells per thread");
 
-// value at grid cell (i, j) of a staged box whose first cell is (x0-2, z0-2)
-struct Box {
-  const float* s;
-  int x0, z0;
-  __device__ __forceinline__ float operator()(int i, int j) const {
-    return s[(j - z0 + 2) * kElBW + (i - x0 + 2)];
+__device__ __forceinline__ f4 ld4(const float* f, unsigned i) {
+  return *reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(f) + i * 4u);
+}
+__device__ __forceinline__ f2 ld2(const float* f, unsigned i) {
+  return *reinterpret_cast<const f2u*>(reinterpret_cast<const char*>(f) + i * 4u);
+}
+__device__ __forceinline__ void st4(float* f, unsigned i, f4 v) {
+  *reinterpret_cast<f4u*>(reinterpret_cast<char*>(f) + i * 4u) = v;
+}
+__device__ __forceinline__ void st2(float* f, unsigned i, f2 v) {
+  *reinterpret_cast<f2u*>(reinterpret_cast<char*>(f) + i * 4u) = v;
+}
+// the same with the non-temporal hint
+__device__ __forceinline__ f4 ld4_nt(const float* f, unsigned i) {
+  return __builtin_nontemporal_load(
+      reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(f) + i * 4u));
+}
+__device__ __forceinline__ void st4_nt(float* f, unsigned i, f4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<f4u*>(reinterpret_cast<char*>(f) + i * 4u));
+}
+__device__ __forceinline__ f4 lds4(const float* s) { return *reinterpret_cast<const f4*>(s); }
+__device__ __forceinline__ f2 lds2(const float* s) { return *reinterpret_cast<const f2*>(s); }
+__device__ __forceinline__ void put4(float* s, f4 v) { *reinterpret_cast<f4*>(s) = v; }
+__device__ __forceinline__ void put2(float* s, f2 v) { *reinterpret_cast<f2*>(s) = v; }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ f2 fma_(f2 a, f2 b, f2 c) {
+  return f2{fmaf(a.x, b.x, c.x), fmaf(a.y, b.y, c.y)};
+}
+__device__ __forceinline__ f4 fma_(f4 a, f4 b, f4 c) {
+  return f4{fmaf(a.x, b.x, c.x), fmaf(a.y, b.y, c.y), fmaf(a.z, b.z, c.z), fmaf(a.w, b.w, c.w)};
+}
+__device__ __forceinline__ f4 fma_(float a, f4 b, f4 c) { return fma_(f4{a, a, a, a}, b, c); }
+// c != 0 ? a : b, per column
+__device__ __forceinline__ float pick(float c, float a, float b) { return c != 0.0f ? a : b; }
+__device__ __forceinline__ f2 pick(f2 c, f2 a, f2 b) {
+  return f2{pick(c.x, a.x, b.x), pick(c.y, a.y, b.y)};
+}
+__device__ __forceinline__ f4 pick(f4 c, f4 a, f4 b) {
+  return f4{pick(c.x, a.x, b.x), pick(c.y, a.y, b.y), pick(c.z, a.z, b.z), pick(c.w, a.w, b.w)};
+}
+__device__ __forceinline__ f4 pick(float c, f4 a, f4 b) { return c != 0.0f ? a : b; }
+
+// The two first derivatives along x of a staged row (times h) at the four own
+// columns c, whose LDS address is `at`:
+// plus  Dx+ f = c1 (f[i+1] - f[i]) + c2 (f[i+2] - f[i-1]), minus Dx- likewise.
+struct XWin {
+  float w[8];
+  __device__ __forceinline__ XWin(const float* at, f4 c) {
+    const f2 l = lds2(at - 2), r = lds2(at + 4);
+    const float v[8] = {l.x, l.y, c.x, c.y, c.z, c.w, r.x, r.y};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = v[i];
   }
+  __device__ __forceinline__ float d(int i) const {
+    return fmaf(C2, w[i + 3] - w[i], C1 * (w[i + 2] - w[i + 1]));
+  }
+  __device__ __forceinline__ f4 plus() const { return f4{d(1), d(2), d(3), d(4)}; }
+  __device__ __forceinline__ f4 minus() const { return f4{d(0), d(1), d(2), d(3)}; }
 };
-
-template <class F>
-__device__ __forceinline__ float bdxp(const F& f, int i, int j) {
-  return fmaf(C2, f(i + 2, j) - f(i - 1, j), C1 * (f(i + 1, j) - f(i, j)));
+// Rows j-2 .. j+2 of a staged column group (row pitch st), own row c: Dz+, Dz-.
+__device__ __forceinline__ f4 zplus(const float* at, int st, f4 c) {
+  return fma_(C2, lds4(at + 2 * st) - lds4(at - st), C1 * (lds4(at + st) - c));
 }
-template <class F>
-__device__ __forceinline__ float bdxm(const F& f, int i, int j) {
-  return fmaf(C2, f(i + 1, j) - f(i - 2, j), C1 * (f(i, j) - f(i - 1, j)));
+__device__ __forceinline__ f4 zminus(const float* at, int st, f4 c) {
+  const f4 m1 = lds4(at - st);
+  return fma_(C2, lds4(at + st) - lds4(at - 2 * st), C1 * (c - m1));
 }
-template <class F>
-__device__ __forceinline__ float bdzp(const F& f, int i, int j) {
-  return fmaf(C2, f(i, j + 2) - f(i, j - 1), C1 * (f(i, j + 1) - f(i, j)));
-}
-template <class F>
-__device__ __forceinline__ float bdzm(const F& f, int i, int j) {
-  return fmaf(C2, f(i, j + 1) - f(i, j - 2), C1 * (f(i, j) - f(i, j - 1)));
-}
-// z derivatives with the free-surface rules on rows 0 and 1
-template <class F>
-__device__ __forceinline__ float bdz_tzz(const F& f, int i, int j, int fs) {
+// z derivatives with the free-surface rules on rows 0 and 1 (fs: this wave has
+// the rows 0..3 under a free surface; j the thread's row)
+__device__ __forceinline__ f4 dz_tzz(const float* at, int st, f4 c, bool fs, int j) {
   if (fs && j == 0)  // tzz[-1] = -tzz[1]
-    return fmaf(C2, f(i, 2), fmaf(C1 + C2, f(i, 1), -C1 * f(i, 0)));
-  return bdzp(f, i, j);
+    return fma_(C2, lds4(at + 2 * st), fma_(C1 + C2, lds4(at + st), -C1 * c));
+  return zplus(at, st, c);
 }
-template <class F>
-__device__ __forceinline__ float bdz_txz(const F& f, int i, int j, int fs) {
+__device__ __forceinline__ f4 dz_txz(const float* at, int st, f4 c, bool fs, int j) {
   if (fs && j == 0)  // txz[-1] = -txz[0], txz[-2] = -txz[1]
-    return fmaf(2.0f * C2, f(i, 1), 2.0f * C1 * f(i, 0));
+    return fma_(2.0f * C2, lds4(at + st), 2.0f * C1 * c);
   if (fs && j == 1)  // txz[-1] = -txz[0]
-    return fmaf(C2, f(i, 2), fmaf(-C1 + C2, f(i, 0), C1 * f(i, 1)));
-  return bdzm(f, i, j);
+    return fma_(C2, lds4(at + st), fma_(-C1 + C2, lds4(at - st), C1 * c));
+  return zminus(at, st, c);
 }
-template <class F>
-__device__ __forceinline__ float bdz_vx(const F& f, int i, int j, int fs) {
-  if (fs && j == 0) return f(i, 1) - f(i, 0);
-  return bdzp(f, i, j);
+__device__ __forceinline__ f4 dz_vx(const float* at, int st, f4 c, bool fs, int j) {
+  if (fs && j == 0) return lds4(at + st) - c;
+  return zplus(at, st, c);
 }
-template <class F>
-__device__ __forceinline__ float bdz_vz(const F& f, int i, int j, int fs) {
-  if (fs && j == 0) return 0.0f;
-  if (fs && j == 1) return f(i, 1) - f(i, 0);
-  return bdzm(f, i, j);
+__device__ __forceinline__ f4 dz_vz(const float* at, int st, f4 c, bool fs, int j) {
+  if (fs && j == 0) return kZ4;
+  if (fs && j == 1) return c - lds4(at - st);
+  return zminus(at, st, c);
 }
 
-// tile and shot of this work-group (1-D launch over tiles x shots)
-struct ElTile {
-  int x0, z0, shot;
-};
-__device__ __forceinline__ ElTile el_tile(const ElStep& a) {
-  const int f = xcd_spread(blockIdx.x, gridDim.x);
-  const int tx = (a.NX + kTX - 1) / kTX, tz = (a.NZ + kElTZ - 1) / kElTZ;
-  const int t = f % (tx * tz);
-  ElTile r;
-  r.shot = f / (tx * tz);
-  r.x0 = (t % tx) * kTX;
-  r.z0 = (t / tx) * kElTZ;
-  return r;
-}
+// The tile of this work-group (1-D launch over tiles x shots) and this thread's
+// cells of it. kCols: what the right edge can cut. 4: NX is a multiple of 4, an
+// item of four columns (two in a column halo) is inside or outside as a whole.
+// 2, 1: NX is even, odd; tiles that lie inside the grid (kFull) still move four
+// columns at a time, at any 4-byte address, and the tiles at the right edge move
+// them in parts of kCols. Guarded loads come from a valid address and are
+// selected afterwards (no branch).
+template <int kCols, bool kFull>
+struct Tile {
+  int NX, NZ, P, top, x0, z0;
+  size_t so;      // first cell of the shot
+  int shot;
+  int wave, c;    // wave (uniform), first own column in the tile
+  int gx, gz, r;  // first own column and row in the grid, row in the tile
 
-// Guarded load without a per-lane branch: every lane loads (from `safe`, any
-// valid address, where !ok) and the value is selected afterwards. Written as a
-// branch, a guarded load must complete before the other path writes its
-// register, which serialises a sequence of them. The reverse kernels address
-// with 64-bit per-lane offsets like this: the scalar-base form (u32at, as in
-// the forward kernels) made their step 3 % slower.
-__device__ __forceinline__ float ldz(const float* f, size_t i, bool ok, const float* safe) {
-  const float v = *(ok ? f + i : safe);
-  return ok ? v : 0.0f;
-}
-
-// Stages NF shot fields on the tile plus the halo: dst[q][box] = src[q][cell].
-template <int NF>
-__device__ __forceinline__ void el_stage(float (*dst)[kElBox], const float* const* src, int x0,
-                                         int z0, int NX, int NZ) {
-  float v[NF][kElK];
-#pragma unroll
-  for (int k = 0; k < kElK; ++k) {
-    const int e = threadIdx.x + k * kThreads;
-    const int r = e / kElBW, c = e - (e / kElBW) * kElBW;
-    const int gx = x0 - 2 + c, gz = z0 - 2 + r;
-    const bool ok = e < kElBox && gx >= 0 && gx < NX && gz >= 0 && gz < NZ;
-    const unsigned q = ok ? (unsigned)(gz * NX + gx) : 0u;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) v[f][k] = ldz32(src[f], q, ok);
+  static __device__ __forceinline__ void origin(const ElStep& a, int f, int& x0, int& z0,
+                                                int& shot) {
+    const int tx = (a.NX + kTX - 1) / kTX, tz = (a.NZ + kElTZ - 1) / kElTZ;
+    shot = f / (tx * tz);
+    const int t = f - shot * (tx * tz);
+    z0 = (t / tx) * kElTZ;
+    x0 = (t % tx) * kTX;
   }
-#pragma unroll
-  for (int k = 0; k < kElK; ++k) {
-    const int e = threadIdx.x + k * kThreads;
-    if (e < kElBox) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) dst[f][e] = v[f][k];
+  __device__ __forceinline__ Tile(const ElStep& a, int x, int z, int s)
+      : NX(a.NX), NZ(a.NZ), P(a.P), top(a.top), x0(x), z0(z), shot(s) {
+    so = (size_t)shot * ((size_t)NX * NZ);
+    wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    c = (int)(threadIdx.x & 15) * 4;
+    r = wave * 4 + ((int)(threadIdx.x & 63) >> 4);
+    gx = x0 + c;
+    gz = z0 + r;
+  }
+  __device__ __forceinline__ bool zin(int z) const { return (unsigned)z < (unsigned)NZ; }
+  __device__ __forceinline__ bool xin(int x) const { return (unsigned)x < (unsigned)NX; }
+  // f at row z, columns x .. x+3 (x within the tile); 0 outside the grid or where !q
+  __device__ __forceinline__ f4 get(const float* f, int z, int x, bool q = true) const {
+    if (kCols == 4 || kFull) {
+      const bool ok = q && zin(z) && (kFull || xin(x));
+      const f4 v = ld4(f, ok ? (unsigned)(z * NX + x) : 0u);
+      return f4{ok ? v.x : 0.0f, ok ? v.y : 0.0f, ok ? v.z : 0.0f, ok ? v.w : 0.0f};
+    }
+    const f2 a = part(f, z, x, q), b = part(f, z, x + 2, q);
+    return f4{a.x, a.y, b.x, b.y};
+  }
+  // two columns, of a column halo too
+  __device__ __forceinline__ f2 part(const float* f, int z, int x, bool q = true) const {
+    if (kCols >= 2) {
+      const bool ok = q && zin(z) && xin(x);
+      const f2 v = ld2(f, ok ? (unsigned)(z * NX + x) : 0u);
+      return f2{ok ? v.x : 0.0f, ok ? v.y : 0.0f};
+    }
+    const bool o0 = q && zin(z) && xin(x), o1 = q && zin(z) && xin(x + 1);
+    const float v0 = u32at(f, o0 ? (unsigned)(z * NX + x) : 0u);
+    const float v1 = u32at(f, o1 ? (unsigned)(z * NX + x + 1) : 0u);
+    return f2{o0 ? v0 : 0.0f, o1 ? v1 : 0.0f};
+  }
+  __device__ __forceinline__ f4 own(const float* f) const { return get(f, gz, gx); }
+  // own cells with the non-temporal hint (no selection: what lies outside the
+  // grid is not used); the right edge's parts go without it
+  __device__ __forceinline__ f4 own_nt(const float* f) const {
+    if (!(kCols == 4 || kFull)) return own(f);
+    return ld4_nt(f, zin(gz) && (kFull || xin(gx)) ? (unsigned)(gz * NX + gx) : 0u);
+  }
+  __device__ __forceinline__ void put_nt(float* f, f4 v) const {
+    if (!(kCols == 4 || kFull))
+      put(f, v);
+    else if (zin(gz) && (kFull || xin(gx)))
+      st4_nt(f, (unsigned)(gz * NX + gx), v);
+  }
+  __device__ __forceinline__ void put(float* f, f4 v) const {
+    if (!zin(gz)) return;
+    const unsigned k = (unsigned)(gz * NX + gx);
+    if (kCols == 4 || kFull) {
+      if (kFull || xin(gx)) st4(f, k, v);
+    } else if (kCols == 2) {
+      if (xin(gx)) st2(f, k, f2{v.x, v.y});
+      if (xin(gx + 2)) st2(f, k + 2, f2{v.z, v.w});
+    } else {
+      if (xin(gx)) u32at(f, k) = v.x;
+      if (xin(gx + 1)) u32at(f, k + 1) = v.y;
+      if (xin(gx + 2)) u32at(f, k + 2) = v.z;
+      if (xin(gx + 3)) u32at(f, k + 3) = v.w;
     }
   }
-}
-
-// Per-thread cell geometry of a tile: column i (clamped ic for loads), rows
-// jb .. jb + kElRZ - 1 (jb is the same for the whole wave, which readfirstlane
-// tells the compiler, so the row coefficients are scalar loads and branches on
-// them are uniform).
-struct ElCells {
-  int i, ic, jb;
-  __device__ __forceinline__ ElCells(const ElTile& T, int NX) {
-    i = T.x0 + (threadIdx.x & 63);
-    ic = min(i, NX - 1);
-    jb = T.z0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * kElRZ;
+  // a table along x, z (0 outside the grid)
+  __device__ __forceinline__ f4 tabx(const float* t) const { return get(t, 0, gx); }
+  __device__ __forceinline__ float tabz(const float* t, int z) const {
+    return ldz32(t, zin(z) ? (unsigned)z : 0u, zin(z));
+  }
+  // C-PML: no coefficient is other than 0 outside columns [0, P) and
+  // [NX - 1 - P, NX), rows [0, top) and [NZ - 1 - P, NZ) (half nodes lie half a
+  // cell further). Whether the tile's columns -2 .. 65 (its rows z .. z+n-1) touch
+  // those, and whether n columns from x (row z) do.
+  __device__ __forceinline__ bool xs() const {
+    return P > 0 && (x0 - 2 < P || x0 + kTX + 2 > NX - 1 - P);
+  }
+  __device__ __forceinline__ bool zs(int z, int n) const {
+    return z < top || (P > 0 && z + n > NZ - 1 - P);
+  }
+  __device__ __forceinline__ bool xq(int x, int n) const { return x < P || x + n > NX - 1 - P; }
+  // halo of this wave: 0 the rows, 1 the columns, other: none
+  __device__ __forceinline__ int role() const { return (wave + (int)blockIdx.x) & 3; }
+  // row halo item (64 lanes): grid row and LDS row; columns as the own ones
+  __device__ __forceinline__ void row_item(int& z, int& lr) const {
+    const int h = (int)(threadIdx.x & 63) >> 4;
+    lr = h < 2 ? h : kElTZ + h;
+    z = z0 - 2 + lr;
+  }
+  // column halo item (32 lanes): grid row and column, LDS row and column
+  __device__ __forceinline__ bool col_item(int& z, int& x, int& lr, int& lc) const {
+    const int l = threadIdx.x & 63;
+    lr = (l >> 1) & 15;
+    z = z0 + lr;
+    x = l & 1 ? x0 + kTX : x0 - 2;
+    lc = l & 1 ? kTX + 4 : 2;
+    return l < 32;
   }
 };
+
+// Runs body<kFull>(tile) for the tile f.
+#define EL_DISPATCH(BODY)                                                     \
+  do {                                                                        \
+    int x0, z0, shot;                                                         \
+    Tile<kCols, true>::origin(a, f, x0, z0, shot);                            \
+    if (kCols != 4 && x0 + kTX <= a.NX)                                       \
+      BODY<kCols, true, kFluid>(a, Tile<kCols, true>(a, x0, z0, shot), sb);   \
+    else                                                                      \
+      BODY<kCols, false, kFluid>(a, Tile<kCols, false>(a, x0, z0, shot), sb); \
+  } while (0)
 
 // The stress update is txx += dt (cxx_x exx + cxx_z ezz), tzz += dt (czz_x exx +
 // czz_z ezz). Away from a free surface cxx_x = czz_z = lambda + 2 mu and
 // cxx_z = czz_x = lambda; on the free-surface row cxx_x = M and the other three
 // are 0. So czz_x = cxx_z everywhere, and czz_z (of row j) follows from cxx_x:
 // the kernels read two coefficient planes instead of four.
-__device__ __forceinline__ float czz_z(const ElStep& a, int j, float cxx_x) {
-  return a.fs && j == 0 ? 0.0f : cxx_x;
+__device__ __forceinline__ f4 czz_z(const ElStep& a, int j, f4 cxx_x) {
+  return a.fs && j == 0 ? kZ4 : cxx_x;
 }
 
-// C-PML update with a preloaded memory variable: psi <- b psi + a G where
-// a != 0 (stored), returns G + psi; G elsewhere.
-__device__ __forceinline__ float cpml_p(float* psi, unsigned k, float G, float a, float b, float p0,
-                                        bool store) {
-  if (a == 0.0f) return G;
-  const float p = fmaf(a, G, b * p0);
-  if (store) u32at(psi, k) = p;
-  return G + p;
+// C-PML update of the own cells with a preloaded memory variable: psi <- b psi +
+// a G where a != 0 (stored with its unchanged neighbours), returns G + psi; G
+// elsewhere. On: whether the wave has a cell where a != 0 may hold, q: the item.
+template <class T, class A>
+__device__ __forceinline__ f4 cpml(const T& t, float* psi, bool on, bool q, f4 G, A a, A b, f4 p0) {
+  if (!on) return G;
+  const f4 p = fma_(a, G, b * p0);
+  if (q) t.put(psi, pick(a, p, p0));
+  return pick(a, G + p, G);
 }
 
 // ---------------------------------------------------------------------------
 // forward: velocity update  vx += dt bx (Dx+ txx + Dz- txz), vz += dt bz (Dx- txz + Dz+ tzz)
-// All global loads of a thread (staging, then its cells' operands and memory
-// variables) are issued before its first store.
 // ---------------------------------------------------------------------------
-template <bool kFluid>
-__global__ __launch_bounds__(256) void el_vel_kernel(ElStep a) {
-  constexpr int NF = kFluid ? 2 : 3;
-  __shared__ float sb[NF][kElBox];
-  const ElTile T = el_tile(a);
-  const int NX = a.NX, NZ = a.NZ;
-  const size_t plane = (size_t)NX * NZ;
-  const size_t so = (size_t)T.shot * plane;
-  {
-    const float* src[3] = {a.txx + so, a.tzz + so, a.txz + so};
-    el_stage<NF>(sb, src, T.x0, T.z0, NX, NZ);
+constexpr int kVelLds = kElTZ * kElXP + kElZH * kTX;  // txx, tzz; txz after them
+
+template <int kCols, bool kFull, bool kFluid>
+__device__ __forceinline__ void el_vel(const ElStep& a, const Tile<kCols, kFull>& t, float* sb) {
+  float* const sxx = sb;
+  float* const szz = sb + kElTZ * kElXP;
+  float* const sxz = sb + kVelLds;
+  const size_t so = t.so;
+  const f4 txx = t.own(a.txx + so), tzz = t.own(a.tzz + so);
+  const f4 txz = kFluid ? kZ4 : t.own(a.txz + so);
+  const int role = t.role();
+  f4 h0 = kZ4, h1 = kZ4;
+  int hz, hx, lr, lc = 0;
+  bool hc = false;
+  if (role == 0) {
+    t.row_item(hz, lr);
+    h0 = t.get(a.tzz + so, hz, t.gx);
+    if (!kFluid) h1 = t.get(a.txz + so, hz, t.gx);
+  } else if (role == 1) {
+    hc = t.col_item(hz, hx, lr, lc);
+    const f2 u = t.part(a.txx + so, hz, hx, hc);
+    h0 = f4{u.x, u.y, 0.0f, 0.0f};
+    if (!kFluid) {
+      const f2 w = t.part(a.txz + so, hz, hx, hc);
+      h1 = f4{w.x, w.y, 0.0f, 0.0f};
+    }
   }
-  const ElCells C(T, NX);
-  const float axh = a.axh[C.ic], bxh = a.bxh[C.ic], axi = a.axi[C.ic], bxi = a.bxi[C.ic];
-  const bool wxh = __any(axh != 0.0f), wxi = __any(axi != 0.0f);
-  float ovx[kElRZ], ovz[kElRZ], cbx[kElRZ], cbz[kElRZ], p0[kElRZ], p1[kElRZ], p2[kElRZ],
-      p3[kElRZ];
-  float azi[kElRZ], bzi[kElRZ], azh[kElRZ], bzh[kElRZ];
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int jc = min(C.jb + r, NZ - 1);
-    const unsigned k = (unsigned)(jc * NX + C.ic);
-    ovx[r] = u32at(a.vx + so, k);
-    ovz[r] = u32at(a.vz + so, k);
-    cbx[r] = u32at(a.bx, k);
-    cbz[r] = u32at(a.bz, k);
-    azi[r] = a.azi[jc];
-    bzi[r] = a.bzi[jc];
-    azh[r] = a.azh[jc];
-    bzh[r] = a.bzh[jc];
-    p0[r] = wxh ? u32at(a.ps[0] + so, k) : 0.0f;
-    p1[r] = !kFluid && azi[r] != 0.0f ? u32at(a.ps[1] + so, k) : 0.0f;
-    p2[r] = !kFluid && wxi ? u32at(a.ps[2] + so, k) : 0.0f;
-    p3[r] = azh[r] != 0.0f ? u32at(a.ps[3] + so, k) : 0.0f;
+  const f4 ovx = t.own(a.vx + so), ovz = t.own(a.vz + so), bx = t.own(a.bx), bz = t.own(a.bz);
+  const bool xs = t.xs(), zs = t.zs(t.z0 + t.wave * 4, 4);
+  const bool xq = t.xq(t.gx, 4), zq = t.zs(t.gz, 1);
+  f4 axh = kZ4, bxh = kZ4, axi = kZ4, bxi = kZ4, p0 = kZ4, p1 = kZ4, p2 = kZ4, p3 = kZ4;
+  float azi = 0.0f, bzi = 0.0f, azh = 0.0f, bzh = 0.0f;
+  if (xs) {
+    p0 = t.get(a.ps[0] + so, t.gz, t.gx, xq);
+    axh = t.tabx(a.axh);
+    bxh = t.tabx(a.bxh);
+    if (!kFluid) {
+      p2 = t.get(a.ps[2] + so, t.gz, t.gx, xq);
+      axi = t.tabx(a.axi);
+      bxi = t.tabx(a.bxi);
+    }
+  }
+  if (zs) {
+    p3 = t.get(a.ps[3] + so, t.gz, t.gx, zq);
+    azh = t.tabz(a.azh, t.gz);
+    bzh = t.tabz(a.bzh, t.gz);
+    if (!kFluid) {
+      p1 = t.get(a.ps[1] + so, t.gz, t.gx, zq);
+      azi = t.tabz(a.azi, t.gz);
+      bzi = t.tabz(a.bzi, t.gz);
+    }
+  }
+  float* const oxx = sxx + t.r * kElXP + 4 + t.c;
+  float* const ozz = szz + (t.r + 2) * kTX + t.c;
+  float* const oxz = sxz + (t.r + 2) * kElXP + 4 + t.c;
+  put4(oxx, txx);
+  put4(ozz, tzz);
+  if (!kFluid) put4(oxz, txz);
+  if (role == 0) {
+    put4(szz + lr * kTX + t.c, h0);
+    if (!kFluid) put4(sxz + lr * kElXP + 4 + t.c, h1);
+  } else if (hc) {
+    put2(sxx + lr * kElXP + lc, f2{h0.x, h0.y});
+    if (!kFluid) put2(sxz + (lr + 2) * kElXP + lc, f2{h1.x, h1.y});
   }
   __syncthreads();
-  const Box txx{sb[0], T.x0, T.z0}, tzz{sb[1], T.x0, T.z0}, txz{sb[NF - 1], T.x0, T.z0};
-  const int i = C.i;
+  const bool fs = a.fs && t.z0 == 0 && t.wave == 0;
   const float ih = a.ih;
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int j = C.jb + r;
-    if (i >= NX || j >= NZ) continue;
-    const unsigned k = (unsigned)(j * NX + i);
-    const float Ga = bdxp(txx, i, j) * ih;
-    const float Gd = bdz_tzz(tzz, i, j, a.fs) * ih;
-    float fvx = cpml_p(a.ps[0] + so, k, Ga, axh, bxh, p0[r], true);
-    float fvz = cpml_p(a.ps[3] + so, k, Gd, azh[r], bzh[r], p3[r], true);
+  const f4 Ga = XWin(oxx, txx).plus() * ih;
+  const f4 Gd = dz_tzz(ozz, kTX, tzz, fs, t.gz) * ih;
+  f4 fvx = cpml(t, a.ps[0] + so, xs, xq, Ga, axh, bxh, p0);
+  f4 fvz = cpml(t, a.ps[3] + so, zs, zq, Gd, azh, bzh, p3);
+  if (!kFluid) {
+    const f4 Gb = dz_txz(oxz, kElXP, txz, fs, t.gz) * ih;
+    const f4 Gc = XWin(oxz, txz).minus() * ih;
+    fvx = fvx + cpml(t, a.ps[1] + so, zs, zq, Gb, azi, bzi, p1);
+    fvz = cpml(t, a.ps[2] + so, xs, xq, Gc, axi, bxi, p2) + fvz;
+  }
+  t.put(a.vx + so, fma_(a.dt * bx, fvx, ovx));
+  t.put(a.vz + so, fma_(a.dt * bz, fvz, ovz));
+  if (a.tr[0]) {
+    t.put_nt(a.tr[0] + so, fvx);
+    t.put_nt(a.tr[1] + so, fvz);
+  }
+}
+
+template <int kCols, bool kFluid>
+__global__ __launch_bounds__(kThreads) void el_vel_kernel(ElStep a) {
+  __shared__ __attribute__((aligned(16))) float sb[kVelLds + (kFluid ? 0 : kElZH * kElXP)];
+  const int f = xcd_spread(blockIdx.x, gridDim.x);
+  EL_DISPATCH(el_vel);
+}
+
+// ---------------------------------------------------------------------------
+// forward: stress update, explosive source and, in the work-groups after the
+// tiles', gathers[shot][n][r] = (vx, vz) at the receiver cell (v^{n+1/2}, which
+// this kernel reads only)
+// ---------------------------------------------------------------------------
+template <int kCols, bool kFull, bool kFluid>
+__device__ __forceinline__ void el_str(const ElStep& a, const Tile<kCols, kFull>& t, float* sb) {
+  float* const svx = sb;
+  float* const svz = sb + kElZH * kElXP;
+  const size_t so = t.so;
+  const f4 vx = t.own(a.vx + so), vz = t.own(a.vz + so);
+  const int role = t.role();
+  f4 h0 = kZ4, h1 = kZ4;
+  int hz, hx, lr, lc = 0;
+  bool hc = false;
+  if (role == 0) {
+    t.row_item(hz, lr);
+    h1 = t.get(a.vz + so, hz, t.gx);
+    if (!kFluid) h0 = t.get(a.vx + so, hz, t.gx);
+  } else if (role == 1) {
+    hc = t.col_item(hz, hx, lr, lc);
+    const f2 u = t.part(a.vx + so, hz, hx, hc);
+    h0 = f4{u.x, u.y, 0.0f, 0.0f};
     if (!kFluid) {
-      const float Gb = bdz_txz(txz, i, j, a.fs) * ih;
-      const float Gc = bdxm(txz, i, j) * ih;
-      fvx = fvx + cpml_p(a.ps[1] + so, k, Gb, azi[r], bzi[r], p1[r], true);
-      fvz = cpml_p(a.ps[2] + so, k, Gc, axi, bxi, p2[r], true) + fvz;
-    }
-    u32at(a.vx + so, k) = fmaf(a.dt * cbx[r], fvx, ovx[r]);
-    u32at(a.vz + so, k) = fmaf(a.dt * cbz[r], fvz, ovz[r]);
-    if (a.tr[0]) {
-      u32at(a.tr[0] + so, k) = fvx;
-      u32at(a.tr[1] + so, k) = fvz;
+      const f2 w = t.part(a.vz + so, hz, hx, hc);
+      h1 = f4{w.x, w.y, 0.0f, 0.0f};
     }
   }
-}
-
-// gathers[shot][n][r] = (vx, vz) at the receiver cell (v^{n+1/2})
-__global__ void el_record_kernel(ElStep a) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= a.nshots * a.nrec) return;
-  const int s = t / a.nrec, r = t - s * a.nrec;
-  const size_t plane = (size_t)a.NX * a.NZ;
-  const size_t k = (size_t)s * plane + a.rec_cell[t];
-  float* d = a.gathers + (((size_t)s * a.nt + a.n) * a.nrec + r) * 2;
-  d[0] = a.vx[k];
-  d[1] = a.vz[k];
-}
-
-// ---------------------------------------------------------------------------
-// forward: stress update and explosive source
-// ---------------------------------------------------------------------------
-template <bool kFluid>
-__global__ __launch_bounds__(256) void el_str_kernel(ElStep a) {
-  __shared__ float sb[2][kElBox];
-  const ElTile T = el_tile(a);
-  const int NX = a.NX, NZ = a.NZ;
-  const size_t plane = (size_t)NX * NZ;
-  const int shot = T.shot;
-  const size_t so = (size_t)shot * plane;
-  {
-    const float* src[2] = {a.vx + so, a.vz + so};
-    el_stage<2>(sb, src, T.x0, T.z0, NX, NZ);
+  const f4 otxx = t.own(a.txx + so), otzz = t.own(a.tzz + so);
+  const f4 otxz = kFluid ? kZ4 : t.own(a.txz + so);
+  const f4 cxx_x = t.own(a.cxx_x), cxx_z = t.own(a.cxx_z);
+  const f4 mxz = kFluid ? kZ4 : t.own(a.mxz);
+  const bool xs = t.xs(), zs = t.zs(t.z0 + t.wave * 4, 4);
+  const bool xq = t.xq(t.gx, 4), zq = t.zs(t.gz, 1);
+  f4 axi = kZ4, bxi = kZ4, axh = kZ4, bxh = kZ4, p4 = kZ4, p5 = kZ4, p6 = kZ4, p7 = kZ4;
+  float azi = 0.0f, bzi = 0.0f, azh = 0.0f, bzh = 0.0f;
+  if (xs) {
+    p4 = t.get(a.ps[4] + so, t.gz, t.gx, xq);
+    axi = t.tabx(a.axi);
+    bxi = t.tabx(a.bxi);
+    if (!kFluid) {
+      p7 = t.get(a.ps[7] + so, t.gz, t.gx, xq);
+      axh = t.tabx(a.axh);
+      bxh = t.tabx(a.bxh);
+    }
   }
-  const ElCells C(T, NX);
-  const float axi = a.axi[C.ic], bxi = a.bxi[C.ic], axh = a.axh[C.ic], bxh = a.bxh[C.ic];
-  const bool wxi = __any(axi != 0.0f), wxh = __any(axh != 0.0f);
-  float otxx[kElRZ], otzz[kElRZ], otxz[kElRZ], cxx_x[kElRZ], cxx_z[kElRZ], mxz[kElRZ],
-      p4[kElRZ], p5[kElRZ], p6[kElRZ], p7[kElRZ];
-  float azi[kElRZ], bzi[kElRZ], azh[kElRZ], bzh[kElRZ];
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int jc = min(C.jb + r, NZ - 1);
-    const unsigned k = (unsigned)(jc * NX + C.ic);
-    otxx[r] = u32at(a.txx + so, k);
-    otzz[r] = u32at(a.tzz + so, k);
-    otxz[r] = kFluid ? 0.0f : u32at(a.txz + so, k);
-    cxx_x[r] = u32at(a.cxx_x, k);
-    cxx_z[r] = u32at(a.cxx_z, k);
-    mxz[r] = kFluid ? 0.0f : u32at(a.mxz, k);
-    azi[r] = a.azi[jc];
-    bzi[r] = a.bzi[jc];
-    azh[r] = a.azh[jc];
-    bzh[r] = a.bzh[jc];
-    p4[r] = wxi ? u32at(a.ps[4] + so, k) : 0.0f;
-    p5[r] = azi[r] != 0.0f ? u32at(a.ps[5] + so, k) : 0.0f;
-    p6[r] = !kFluid && azh[r] != 0.0f ? u32at(a.ps[6] + so, k) : 0.0f;
-    p7[r] = !kFluid && wxh ? u32at(a.ps[7] + so, k) : 0.0f;
+  if (zs) {
+    p5 = t.get(a.ps[5] + so, t.gz, t.gx, zq);
+    azi = t.tabz(a.azi, t.gz);
+    bzi = t.tabz(a.bzi, t.gz);
+    if (!kFluid) {
+      p6 = t.get(a.ps[6] + so, t.gz, t.gx, zq);
+      azh = t.tabz(a.azh, t.gz);
+      bzh = t.tabz(a.bzh, t.gz);
+    }
   }
-  const int src = a.src_cell[shot];
-  const float sw = a.w * a.wavelet[(size_t)shot * a.nt + a.n];
+  const int src = a.src_cell[t.shot];
+  const float sw = a.w * a.wavelet[(size_t)t.shot * a.nt + a.n];
+  float* const ox = svx + (t.r + 2) * kElXP + 4 + t.c;
+  float* const oz = svz + (t.r + 2) * kElXP + 4 + t.c;
+  put4(ox, vx);
+  put4(oz, vz);
+  if (role == 0) {
+    put4(svz + lr * kElXP + 4 + t.c, h1);
+    if (!kFluid) put4(svx + lr * kElXP + 4 + t.c, h0);
+  } else if (hc) {
+    put2(svx + (lr + 2) * kElXP + lc, f2{h0.x, h0.y});
+    if (!kFluid) put2(svz + (lr + 2) * kElXP + lc, f2{h1.x, h1.y});
+  }
   __syncthreads();
-  const Box vx{sb[0], T.x0, T.z0}, vz{sb[1], T.x0, T.z0};
-  const int i = C.i;
+  const bool fs = a.fs && t.z0 == 0 && t.wave == 0;
   const float ih = a.ih, dt = a.dt;
+  const f4 Ge = XWin(ox, vx).minus() * ih;
+  const f4 Gf = dz_vz(oz, kElXP, vz, fs, t.gz) * ih;
+  const f4 exx = cpml(t, a.ps[4] + so, xs, xq, Ge, axi, bxi, p4);
+  const f4 ezz = cpml(t, a.ps[5] + so, zs, zq, Gf, azi, bzi, p5);
+  f4 txx = otxx + dt * fma_(cxx_x, exx, cxx_z * ezz);
+  f4 tzz = otzz + dt * fma_(cxx_z, exx, czz_z(a, t.gz, cxx_x) * ezz);
+  const int sc = src - (t.gz * t.NX + t.gx);
+  if ((unsigned)sc < 4u && t.xin(t.gx + sc)) {
+    const float sz = sw * u32at(a.smask, (unsigned)src);
 #pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int j = C.jb + r;
-    if (i >= NX || j >= NZ) continue;
-    const unsigned k = (unsigned)(j * NX + i);
-    const float Ge = bdxm(vx, i, j) * ih;
-    const float Gf = bdz_vz(vz, i, j, a.fs) * ih;
-    const float exx = cpml_p(a.ps[4] + so, k, Ge, axi, bxi, p4[r], true);
-    const float ezz = cpml_p(a.ps[5] + so, k, Gf, azi[r], bzi[r], p5[r], true);
-    float txx = otxx[r] + dt * fmaf(cxx_x[r], exx, cxx_z[r] * ezz);
-    float tzz = otzz[r] + dt * fmaf(cxx_z[r], exx, czz_z(a, j, cxx_x[r]) * ezz);
-    if ((int)k == src) {
-      txx += sw;
-      tzz += sw * u32at(a.smask, k);
-    }
-    u32at(a.txx + so, k) = txx;
-    u32at(a.tzz + so, k) = tzz;
-    if (a.tr[2]) {
-      u32at(a.tr[2] + so, k) = exx;
-      u32at(a.tr[3] + so, k) = ezz;
-    }
-    if (!kFluid) {
-      const float Gg = bdz_vx(vx, i, j, a.fs) * ih;
-      const float Gh = bdxp(vz, i, j) * ih;
-      const float exz = cpml_p(a.ps[6] + so, k, Gg, azh[r], bzh[r], p6[r], true) +
-                        cpml_p(a.ps[7] + so, k, Gh, axh, bxh, p7[r], true);
-      u32at(a.txz + so, k) = fmaf(dt * mxz[r], exz, otxz[r]);
-      if (a.tr[2]) u32at(a.tr[4] + so, k) = exz;
-    }
+    for (int q = 0; q < 4; ++q)
+      if (q == sc) {
+        txx[q] += sw;
+        tzz[q] += sz;
+      }
   }
+  t.put(a.txx + so, txx);
+  t.put(a.tzz + so, tzz);
+  f4 exz = kZ4;
+  if (!kFluid) {
+    const f4 Gg = dz_vx(ox, kElXP, vx, fs, t.gz) * ih;
+    const f4 Gh = XWin(oz, vz).plus() * ih;
+    exz = cpml(t, a.ps[6] + so, zs, zq, Gg, azh, bzh, p6) +
+          cpml(t, a.ps[7] + so, xs, xq, Gh, axh, bxh, p7);
+    t.put(a.txz + so, fma_(dt * mxz, exz, otxz));
+  }
+  if (a.tr[2]) {
+    t.put_nt(a.tr[2] + so, exx);
+    t.put_nt(a.tr[3] + so, ezz);
+    if (!kFluid) t.put_nt(a.tr[4] + so, exz);
+  }
+}
+
+template <int kCols, bool kFluid>
+__global__ __launch_bounds__(kThreads) void el_str_kernel(ElStep a, int ntiles) {
+  __shared__ __attribute__((aligned(16))) float sb[2 * kElZH * kElXP];
+  if ((int)blockIdx.x >= ntiles) {
+    const size_t t = (size_t)(blockIdx.x - ntiles) * kThreads + threadIdx.x;
+    if (t >= (size_t)a.nshots * a.nrec) return;
+    const int s = (int)(t / a.nrec), r = (int)(t - (size_t)s * a.nrec);
+    const size_t k = (size_t)s * ((size_t)a.NX * a.NZ) + a.rec_cell[t];
+    float* d = a.gathers + (((size_t)s * a.nt + a.n) * a.nrec + r) * 2;
+    d[0] = a.vx[k];
+    d[1] = a.vz[k];
+    return;
+  }
+  const int f = xcd_spread(blockIdx.x, ntiles);
+  EL_DISPATCH(el_str);
 }
 
 // ---------------------------------------------------------------------------
@@ -348,358 +536,381 @@ __global__ __launch_bounds__(256) void el_str_kernel(ElStep a) {
 // Psi <- b t. The velocity adjoints collect the transposed derivatives of those.
 // ---------------------------------------------------------------------------
 
-// Transposed z-derivative of g at row j: standard (-Dz- or -Dz+) away from a
-// free surface, otherwise the host-derived taps of the first four rows (their
-// offsets lie within two rows).
-template <class F>
-__device__ __forceinline__ float dzT(const ElStep& a, int kind, int j, F g, bool minus_dzm) {
-  if (a.fs && j < 4) {
-    float acc = 0.0f;
-    const int n = a.tt_cnt[kind][j];
-    for (int e = 0; e < n; ++e) acc = fmaf(a.tt_w[kind][j][e], g(j + a.tt_off[kind][j][e]), acc);
+// Transposed z-derivative of a staged plane (column group `at`, own row c, row
+// pitch kTX) at row j: standard (-Dz- or -Dz+) away from a free surface,
+// otherwise (fs: the wave of the first four rows) the host-derived taps, whose
+// offsets lie within two rows.
+__device__ __forceinline__ f4 dzT(const ElStep& a, int kind, const float* at, f4 c, bool fs, int j,
+                                  bool minus_dzm) {
+  if (fs) {
+    f4 acc = kZ4;
+    const int n = a.tt_cnt[kind][j & 3];
+    for (int e = 0; e < n; ++e)
+      acc = fma_(a.tt_w[kind][j & 3][e], lds4(at + a.tt_off[kind][j & 3][e] * kTX), acc);
     return acc;
   }
-  // -(Dz-) g = -[c1 (g_j - g_{j-1}) + c2 (g_{j+1} - g_{j-2})]
-  // -(Dz+) g = -[c1 (g_{j+1} - g_j) + c2 (g_{j+2} - g_{j-1})]
-  if (minus_dzm) return -fmaf(C2, g(j + 1) - g(j - 2), C1 * (g(j) - g(j - 1)));
-  return -fmaf(C2, g(j + 2) - g(j - 1), C1 * (g(j + 1) - g(j)));
+  return minus_dzm ? -zminus(at, kTX, c) : -zplus(at, kTX, c);
 }
 
-// The reverse kernels split the box cells of a tile between the threads: a
-// thread stages its own cells (box column lx + 2, rows kElRZ w + 2 ..
-// kElRZ w + kElRZ + 1) and keeps their raw values in registers for its own
-// update, and up to kElKH of the kElHalo halo cells (the two rows above and
-// below the tile, the two columns left and right of it). Reading its own
-// cells again after the LDS phase would miss L2: by then the other resident
-// work-groups' reads have evicted them.
-constexpr int kElHalo = kElBox - kTX * kElTZ;
-constexpr int kElKH = (kElHalo + kThreads - 1) / kThreads;
-static_assert(kElBW == kTX + 4 && kElBH == kElTZ + 4 && kThreads == 4 * kTX, "tile geometry");
-
-// box index of halo cell h < kElHalo
-__device__ __forceinline__ int el_halo_cell(int h) {
-  if (h < 2 * kElBW) return h;                                // rows 0, 1
-  if (h < 4 * kElBW) return h + (kElBH - 4) * kElBW;          // the last two rows
-  const int q = h - 4 * kElBW, c = q & 3;                     // columns 0, 1, 66, 67
-  return (2 + (q >> 2)) * kElBW + (c < 2 ? c : kTX + c);
-}
-// box index of this thread's own cell in row r of its rows
-__device__ __forceinline__ int el_own_cell(int r) {
-  return ((int)(threadIdx.x >> 6) * kElRZ + r + 2) * kElBW + (int)(threadIdx.x & 63) + 2;
+// Derivative-input adjoint e + a (q + e) where a != 0, e elsewhere.
+template <class F, class A>
+__device__ __forceinline__ F adj_in(A a, F q, F e) {
+  return pick(a, fma_(a, q + e, e), e);
 }
 
-// Raw inputs of one box cell of the stress-adjoint staging (zero outside the
-// grid or where !valid; every lane takes part, as the C-PML tests are votes
-// of the wave).
-struct AdjS {
-  float txx, tzz, txz, cxx_x, czz_x, cxx_z, czz_z, mxz, ax, az, azh, axh, q4, q5, q6, q7;
-};
-template <bool kFluid>
-__device__ __forceinline__ void adj_s_load(const ElStep& a, size_t so, int e, bool valid, int x0,
-                                           int z0, AdjS& v) {
-  const int r = e / kElBW, c = e - (e / kElBW) * kElBW;
-  const int gx = x0 - 2 + c, gz = z0 - 2 + r;
-  const bool ok = valid && gx >= 0 && gx < a.NX && gz >= 0 && gz < a.NZ;
-  const size_t q = ok ? (size_t)gz * a.NX + gx : 0;
-  const int cx = ok ? gx : 0, cz = ok ? gz : 0;
-  v.txx = ldz(a.txx + so, q, ok, a.txx);
-  v.tzz = ldz(a.tzz + so, q, ok, a.tzz);
-  v.txz = kFluid ? 0.0f : ldz(a.txz + so, q, ok, a.txz);
-  v.cxx_x = ldz(a.cxx_x, q, ok, a.cxx_x);
-  v.cxx_z = ldz(a.cxx_z, q, ok, a.cxx_z);
-  v.czz_x = v.cxx_z;
-  v.czz_z = czz_z(a, gz, v.cxx_x);
-  v.mxz = kFluid ? 0.0f : ldz(a.mxz, q, ok, a.mxz);
-  v.ax = ldz(a.axi, cx, ok, a.axi);
-  v.az = ldz(a.azi, cz, ok, a.azi);
-  v.azh = kFluid ? 0.0f : ldz(a.azh, cz, ok, a.azh);
-  v.axh = kFluid ? 0.0f : ldz(a.axh, cx, ok, a.axh);
-  // memory variables only where a wave has a C-PML cell (wave-uniform branch)
-  v.q4 = __any(v.ax != 0.0f) ? ldz(a.ps_in[4] + so, q, ok, a.ps_in[4]) : 0.0f;
-  v.q5 = __any(v.az != 0.0f) ? ldz(a.ps_in[5] + so, q, ok, a.ps_in[5]) : 0.0f;
-  v.q6 = !kFluid && __any(v.azh != 0.0f) ? ldz(a.ps_in[6] + so, q, ok, a.ps_in[6]) : 0.0f;
-  v.q7 = !kFluid && __any(v.axh != 0.0f) ? ldz(a.ps_in[7] + so, q, ok, a.ps_in[7]) : 0.0f;
-}
-// ebar of the three stress-step inputs: dt (stress coefficients) x (stress adjoints)
-__device__ __forceinline__ float adj_ex(const AdjS& v, float dt) {
-  return dt * fmaf(v.cxx_x, v.txx, v.czz_x * v.tzz);
-}
-__device__ __forceinline__ float adj_ez(const AdjS& v, float dt) {
-  return dt * fmaf(v.cxx_z, v.txx, v.czz_z * v.tzz);
-}
-__device__ __forceinline__ float adj_exz(const AdjS& v, float dt) { return dt * v.mxz * v.txz; }
-
-// derivative-input adjoints gbe (exx input), gbf (ezz), gbg (Dz vx of exz),
-// gbh (Dx vz of exz) of box cell e (outside the grid every operand is 0, so
-// every value is 0 too)
-template <bool kFluid>
-__device__ __forceinline__ void adj_s_put(float (*sb)[kElBox], int e, float dt, const AdjS& v) {
-  const float e1 = adj_ex(v, dt), e2 = adj_ez(v, dt);
-  sb[0][e] = v.ax == 0.0f ? e1 : fmaf(v.ax, v.q4 + e1, e1);
-  sb[1][e] = v.az == 0.0f ? e2 : fmaf(v.az, v.q5 + e2, e2);
-  if (!kFluid) {
-    const float e3 = adj_exz(v, dt);
-    sb[2][e] = v.azh == 0.0f ? e3 : fmaf(v.azh, v.q6 + e3, e3);
-    sb[3][e] = v.axh == 0.0f ? e3 : fmaf(v.axh, v.q7 + e3, e3);
-  }
+// The memory-variable adjoint b (q + e) of the own cells (0 where a = 0, where
+// it is never used).
+template <class T, class A>
+__device__ __forceinline__ void adj_psi(const T& t, float* out, bool on, bool q, A a, A b, f4 q0,
+                                        f4 e) {
+  if (on && q) t.put(out, pick(a, b * (q0 + e), kZ4));
 }
 
-template <bool kFluid>
-__global__ __launch_bounds__(256) void el_adj_s_kernel(ElStep a) {
-  __shared__ float sb[kFluid ? 2 : 4][kElBox];
-  const ElTile T = el_tile(a);
-  const int NX = a.NX, NZ = a.NZ;
-  const size_t plane = (size_t)NX * NZ;
-  const size_t so = (size_t)T.shot * plane;
+constexpr int kAdjX = kElTZ * kElXP, kAdjZ = kElZH * kTX;  // LDS planes with an x, a z halo
+
+// Velocity adjoints from the stress adjoints, coefficient gradients, then the
+// residuals of the receivers in the tile.
+template <int kCols, bool kFull, bool kFluid>
+__device__ __forceinline__ void el_adj_s(const ElStep& a, const Tile<kCols, kFull>& t, float* sb) {
+  float* const sbe = sb;                  // exx input, x halo
+  float* const sbf = sb + kAdjX;          // ezz input, z halo
+  float* const sbg = sbf + kAdjZ;         // Dz vx of exz, z halo
+  float* const sbh = sbg + kAdjZ;         // Dx vz of exz, x halo
+  const size_t so = t.so;
   const float dt = a.dt, ih = a.ih;
-  AdjS hv[kElKH], ov[kElRZ];
-#pragma unroll
-  for (int k = 0; k < kElKH; ++k) {
-    const int h = (int)threadIdx.x + k * kThreads;
-    adj_s_load<kFluid>(a, so, h < kElHalo ? el_halo_cell(h) : 0, h < kElHalo, T.x0, T.z0,
-                       hv[k]);
-  }
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r)
-    adj_s_load<kFluid>(a, so, el_own_cell(r), true, T.x0, T.z0, ov[r]);
-#pragma unroll
-  for (int k = 0; k < kElKH; ++k) {
-    const int h = (int)threadIdx.x + k * kThreads;
-    if (h < kElHalo) adj_s_put<kFluid>(sb, el_halo_cell(h), dt, hv[k]);
-  }
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) adj_s_put<kFluid>(sb, el_own_cell(r), dt, ov[r]);
-  const ElCells C(T, NX);
-  const float bxi = a.bxi[C.ic], bxh = a.bxh[C.ic];
-  const bool gacc = !a.g_init;
-  float ovx[kElRZ], ovz[kElRZ], fexx[kElRZ], fezz[kElRZ], fexz[kElRZ], g0[kElRZ], g1[kElRZ],
-      g2[kElRZ], bzi[kElRZ], bzh[kElRZ];
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int jc = min(C.jb + r, NZ - 1);
-    const size_t k = (size_t)jc * NX + C.ic;
-    ovx[r] = a.vx[so + k];
-    ovz[r] = a.vz[so + k];
-    bzi[r] = a.bzi[jc];
-    bzh[r] = a.bzh[jc];
-    fexx[r] = a.trc[2][so + k];
-    fezz[r] = a.trc[3][so + k];
-    fexz[r] = kFluid ? 0.0f : a.trc[4][so + k];
-    g0[r] = gacc ? a.g[0][so + k] : 0.0f;
-    g1[r] = !kFluid && gacc ? a.g[1][so + k] : 0.0f;
-    g2[r] = !kFluid && gacc ? a.g[2][so + k] : 0.0f;
-  }
-  const float dml = a.fs ? a.dM_dl[C.ic] : 0.0f, dmm = a.fs ? a.dM_dm[C.ic] : 0.0f;
-  __syncthreads();
-  const Box gbe{sb[0], T.x0, T.z0}, gbf{sb[1], T.x0, T.z0}, gbg{sb[kFluid ? 0 : 2], T.x0, T.z0},
-      gbh{sb[kFluid ? 1 : 3], T.x0, T.z0};
-  const int i = C.i;
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int j = C.jb + r;
-    if (i >= NX || j >= NZ) continue;
-    const size_t k = (size_t)j * NX + i;
-    // Vx += (Dx-)^T gbe + (Dz+ of vx)^T gbg ;  (Dx-)^T = -Dx+
-    // (the exz terms are absent in a fluid)
-    const float dxe = -fmaf(C2, gbe(i + 2, j) - gbe(i - 1, j), C1 * (gbe(i + 1, j) - gbe(i, j)));
-    // Vz += (Dz- of vz)^T gbf + (Dx+)^T gbh ;  (Dx+)^T = -Dx-
-    const float dzf = dzT(a, 3, j, [&](int jj) { return gbf(i, jj); }, false);
-    if (kFluid) {
-      a.vx[so + k] = ovx[r] + dxe * ih;
-      a.vz[so + k] = ovz[r] + dzf * ih;
-    } else {
-      const float dzg = dzT(a, 2, j, [&](int jj) { return gbg(i, jj); }, true);
-      const float dxh =
-          -fmaf(C2, gbh(i + 1, j) - gbh(i - 2, j), C1 * (gbh(i, j) - gbh(i - 1, j)));
-      a.vx[so + k] = ovx[r] + (dxe + dzg) * ih;
-      a.vz[so + k] = ovz[r] + (dzf + dxh) * ih;
-    }
-
-    // own cell: memory-variable adjoints and the coefficient gradients
-    const AdjS& v = ov[r];
-    const float ex = adj_ex(v, dt), ez = adj_ez(v, dt), exz = adj_exz(v, dt);
-    if (v.ax != 0.0f) a.ps_out[4][so + k] = bxi * (v.q4 + ex);
-    if (v.az != 0.0f) a.ps_out[5][so + k] = bzi[r] * (v.q5 + ez);
-    if (!kFluid && v.azh != 0.0f) a.ps_out[6][so + k] = bzh[r] * (v.q6 + exz);
-    if (!kFluid && v.axh != 0.0f) a.ps_out[7][so + k] = bxh * (v.q7 + exz);
-    float glam, gmu;
-    if (a.fs && j == 0) {
-      // txx += dt M exx with M = 4 mu (lambda + mu) / (lambda + 2 mu)
-      const float gM = dt * v.txx * fexx[r];
-      glam = gM * dml;
-      gmu = gM * dmm;
-    } else {
-      glam = dt * (v.txx + v.tzz) * (fexx[r] + fezz[r]);
-      gmu = 2.0f * dt * fmaf(v.txx, fexx[r], v.tzz * fezz[r]);
-    }
-    // a fluid has no mu partials (the gradient finish weighs them by vs = 0;
-    // their planes stay zero)
-    const float gmxz = dt * v.txz * fexz[r];
-    if (a.g_init) {
-      a.g[0][so + k] = glam;
-      if (!kFluid) {
-        a.g[1][so + k] = gmu;
-        a.g[2][so + k] = gmxz;
-      }
-    } else {
-      a.g[0][so + k] = g0[r] + glam;
-      if (!kFluid) {
-        a.g[1][so + k] = g1[r] + gmu;
-        a.g[2][so + k] = g2[r] + gmxz;
-      }
-    }
-  }
-}
-
-// residual injection into the velocity adjoints: entries sorted by (shot, cell, r);
-// the first entry of each run of equal cells adds the whole run in order.
-__global__ void el_inject_kernel(ElStep a, int n) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int tot = a.nshots * a.nrec;
-  if (e >= tot) return;
-  const int4 en = a.rec_sorted[e];  // (shot, cell, r, -)
-  if (e > 0) {
-    const int4 pv = a.rec_sorted[e - 1];
-    if (pv.x == en.x && pv.y == en.y) return;
-  }
-  const size_t plane = (size_t)a.NX * a.NZ;
-  const size_t k = (size_t)en.x * plane + en.y;
-  float ax = a.vx[k], az = a.vz[k];
-  for (int q = e; q < tot; ++q) {
-    const int4 c = a.rec_sorted[q];
-    if (c.x != en.x || c.y != en.y) break;
-    const float* r = a.resid + (((size_t)c.x * a.nt + n) * a.nrec + c.z) * 2;
-    ax += r[0];
-    az += r[1];
-  }
-  a.vx[k] = ax;
-  a.vz[k] = az;
-}
-
-// Raw inputs of one box cell of the velocity-adjoint staging (as AdjS).
-struct AdjV {
-  float vx, vz, bx, bz, axh, az, ax, azh, q0, q1, q2, q3;
-};
-template <bool kFluid>
-__device__ __forceinline__ void adj_v_load(const ElStep& a, size_t so, int e, bool valid, int x0,
-                                           int z0, AdjV& v) {
-  const int r = e / kElBW, c = e - (e / kElBW) * kElBW;
-  const int gx = x0 - 2 + c, gz = z0 - 2 + r;
-  const bool ok = valid && gx >= 0 && gx < a.NX && gz >= 0 && gz < a.NZ;
-  const size_t q = ok ? (size_t)gz * a.NX + gx : 0;
-  const int cx = ok ? gx : 0, cz = ok ? gz : 0;
-  v.vx = ldz(a.vx + so, q, ok, a.vx);
-  v.vz = ldz(a.vz + so, q, ok, a.vz);
-  v.bx = ldz(a.bx, q, ok, a.bx);
-  v.bz = ldz(a.bz, q, ok, a.bz);
-  v.axh = ldz(a.axh, cx, ok, a.axh);
-  v.az = kFluid ? 0.0f : ldz(a.azi, cz, ok, a.azi);
-  v.ax = kFluid ? 0.0f : ldz(a.axi, cx, ok, a.axi);
-  v.azh = ldz(a.azh, cz, ok, a.azh);
-  v.q0 = __any(v.axh != 0.0f) ? ldz(a.ps_in[0] + so, q, ok, a.ps_in[0]) : 0.0f;
-  v.q1 = !kFluid && __any(v.az != 0.0f) ? ldz(a.ps_in[1] + so, q, ok, a.ps_in[1]) : 0.0f;
-  v.q2 = !kFluid && __any(v.ax != 0.0f) ? ldz(a.ps_in[2] + so, q, ok, a.ps_in[2]) : 0.0f;
-  v.q3 = __any(v.azh != 0.0f) ? ldz(a.ps_in[3] + so, q, ok, a.ps_in[3]) : 0.0f;
-}
-// derivative-input adjoints of the velocity step: gba (Dx txx of vx), gbb (Dz
-// txz of vx), gbc (Dx txz of vz), gbd (Dz tzz of vz)
-// (a fluid keeps gba and gbd only, in planes 0 and 1)
-template <bool kFluid>
-__device__ __forceinline__ void adj_v_put(float (*sb)[kElBox], int e, float dt, const AdjV& v) {
-  const float kx = dt * v.bx * v.vx;
-  const float kz = dt * v.bz * v.vz;
-  sb[0][e] = v.axh == 0.0f ? kx : fmaf(v.axh, v.q0 + kx, kx);
-  sb[kFluid ? 1 : 3][e] = v.azh == 0.0f ? kz : fmaf(v.azh, v.q3 + kz, kz);
-  if (!kFluid) {
-    sb[1][e] = v.az == 0.0f ? kx : fmaf(v.az, v.q1 + kx, kx);
-    sb[2][e] = v.ax == 0.0f ? kz : fmaf(v.ax, v.q2 + kz, kz);
-  }
-}
-
-template <bool kFluid>
-__global__ __launch_bounds__(256) void el_adj_v_kernel(ElStep a) {
-  __shared__ float sb[kFluid ? 2 : 4][kElBox];
-  const ElTile T = el_tile(a);
-  const int NX = a.NX, NZ = a.NZ;
-  const size_t plane = (size_t)NX * NZ;
-  const size_t so = (size_t)T.shot * plane;
-  const float dt = a.dt, ih = a.ih;
-  AdjV hv[kElKH], ov[kElRZ];
-#pragma unroll
-  for (int k = 0; k < kElKH; ++k) {
-    const int h = (int)threadIdx.x + k * kThreads;
-    adj_v_load<kFluid>(a, so, h < kElHalo ? el_halo_cell(h) : 0, h < kElHalo, T.x0, T.z0,
-                       hv[k]);
-  }
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r)
-    adj_v_load<kFluid>(a, so, el_own_cell(r), true, T.x0, T.z0, ov[r]);
-#pragma unroll
-  for (int k = 0; k < kElKH; ++k) {
-    const int h = (int)threadIdx.x + k * kThreads;
-    if (h < kElHalo) adj_v_put<kFluid>(sb, el_halo_cell(h), dt, hv[k]);
-  }
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) adj_v_put<kFluid>(sb, el_own_cell(r), dt, ov[r]);
-  const ElCells C(T, NX);
-  const float bxh = a.bxh[C.ic], bxi = a.bxi[C.ic];
-  const bool gacc = !a.g_init;
-  float otxx[kElRZ], otzz[kElRZ], otxz[kElRZ], f0[kElRZ], f1[kElRZ], g3[kElRZ], g4[kElRZ],
-      bzi[kElRZ], bzh[kElRZ];
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int jc = min(C.jb + r, NZ - 1);
-    const size_t k = (size_t)jc * NX + C.ic;
-    otxx[r] = a.txx[so + k];
-    otzz[r] = a.tzz[so + k];
-    otxz[r] = kFluid ? 0.0f : a.txz[so + k];
-    bzi[r] = a.bzi[jc];
-    bzh[r] = a.bzh[jc];
-    f0[r] = a.trc[0][so + k];
-    f1[r] = a.trc[1][so + k];
-    g3[r] = gacc ? a.g[3][so + k] : 0.0f;
-    g4[r] = gacc ? a.g[4][so + k] : 0.0f;
-  }
-  __syncthreads();
-  const Box gba{sb[0], T.x0, T.z0}, gbb{sb[1], T.x0, T.z0}, gbc{sb[kFluid ? 0 : 2], T.x0, T.z0},
-      gbd{sb[kFluid ? 1 : 3], T.x0, T.z0};
-  const int i = C.i;
-#pragma unroll
-  for (int r = 0; r < kElRZ; ++r) {
-    const int j = C.jb + r;
-    if (i >= NX || j >= NZ) continue;
-    const size_t k = (size_t)j * NX + i;
-    // Txx += (Dx+)^T gba = -Dx- gba
-    const float dxa = -fmaf(C2, gba(i + 1, j) - gba(i - 2, j), C1 * (gba(i, j) - gba(i - 1, j)));
-    // Tzz += (Dz+ of tzz)^T gbd
-    const float dzd = dzT(a, 0, j, [&](int jj) { return gbd(i, jj); }, true);
-    a.txx[so + k] = otxx[r] + dxa * ih;
-    a.tzz[so + k] = otzz[r] + dzd * ih;
+  const int role = t.role();
+  const bool xs = t.xs();
+  // this thread's halo item: stress adjoints, coefficients, memory variables
+  f4 hs0 = kZ4, hs1 = kZ4, hs2 = kZ4, hc0 = kZ4, hc1 = kZ4, hc2 = kZ4, hq0 = kZ4, hq1 = kZ4;
+  f4 ha0 = kZ4, ha1 = kZ4;
+  int hz, hx, lr, lc = 0;
+  bool hc = false;
+  if (role == 0) {
+    t.row_item(hz, lr);
+    hs0 = t.get(a.txx + so, hz, t.gx);
+    hs1 = t.get(a.tzz + so, hz, t.gx);
+    hc0 = t.get(a.cxx_x, hz, t.gx);
+    hc1 = t.get(a.cxx_z, hz, t.gx);
     if (!kFluid) {
-      // Txz += (Dz- of txz)^T gbb + (Dx-)^T gbc = ... - Dx+ gbc (a fluid's txz
-      // adjoint reaches nothing: its only use is weighed by mu = 0)
-      const float dzb = dzT(a, 1, j, [&](int jj) { return gbb(i, jj); }, false);
-      const float dxc =
-          -fmaf(C2, gbc(i + 2, j) - gbc(i - 1, j), C1 * (gbc(i + 1, j) - gbc(i, j)));
-      a.txz[so + k] = otxz[r] + (dzb + dxc) * ih;
+      hs2 = t.get(a.txz + so, hz, t.gx);
+      hc2 = t.get(a.mxz, hz, t.gx);
     }
-
-    const AdjV& v = ov[r];
-    const float kx = dt * v.bx * v.vx, kz = dt * v.bz * v.vz;
-    if (v.axh != 0.0f) a.ps_out[0][so + k] = bxh * (v.q0 + kx);
-    if (!kFluid && v.az != 0.0f) a.ps_out[1][so + k] = bzi[r] * (v.q1 + kx);
-    if (!kFluid && v.ax != 0.0f) a.ps_out[2][so + k] = bxi * (v.q2 + kz);
-    if (v.azh != 0.0f) a.ps_out[3][so + k] = bzh[r] * (v.q3 + kz);
-    const float gbx = dt * v.vx * f0[r];
-    const float gbz = dt * v.vz * f1[r];
-    if (a.g_init) {
-      a.g[3][so + k] = gbx;
-      a.g[4][so + k] = gbz;
-    } else {
-      a.g[3][so + k] = g3[r] + gbx;
-      a.g[4][so + k] = g4[r] + gbz;
+    if (t.zs(t.z0 - 2, 2) || t.zs(t.z0 + kElTZ, 2)) {
+      const bool q = t.zs(hz, 1);
+      hq0 = t.get(a.ps_in[5] + so, hz, t.gx, q);
+      ha0.x = t.tabz(a.azi, hz);
+      if (!kFluid) {
+        hq1 = t.get(a.ps_in[6] + so, hz, t.gx, q);
+        ha1.x = t.tabz(a.azh, hz);
+      }
+    }
+  } else if (role == 1) {
+    hc = t.col_item(hz, hx, lr, lc);
+    auto two = [&](const float* f, bool q) {
+      const f2 v = t.part(f, hz, hx, hc && q);
+      return f4{v.x, v.y, 0.0f, 0.0f};
+    };
+    hs0 = two(a.txx + so, true);
+    hs1 = two(a.tzz + so, true);
+    hc0 = two(a.cxx_x, true);
+    hc1 = two(a.cxx_z, true);
+    if (!kFluid) {
+      hs2 = two(a.txz + so, true);
+      hc2 = two(a.mxz, true);
+    }
+    if (xs) {
+      const bool q = t.xq(hx, 2);
+      const f2 u = t.part(a.axi, 0, hx, hc);
+      hq0 = two(a.ps_in[4] + so, q);
+      ha0 = f4{u.x, u.y, 0.0f, 0.0f};
+      if (!kFluid) {
+        const f2 w = t.part(a.axh, 0, hx, hc);
+        hq1 = two(a.ps_in[7] + so, q);
+        ha1 = f4{w.x, w.y, 0.0f, 0.0f};
+      }
     }
   }
+  const f4 txx = t.own(a.txx + so), tzz = t.own(a.tzz + so);
+  const f4 cxx_x = t.own(a.cxx_x), cxx_z = t.own(a.cxx_z);
+  const f4 txz = kFluid ? kZ4 : t.own(a.txz + so), mxz = kFluid ? kZ4 : t.own(a.mxz);
+  const bool zs = t.zs(t.z0 + t.wave * 4, 4);
+  const bool xq = t.xq(t.gx, 4), zq = t.zs(t.gz, 1);
+  f4 axi = kZ4, axh = kZ4, q4 = kZ4, q5 = kZ4, q6 = kZ4, q7 = kZ4;
+  float azi = 0.0f, azh = 0.0f;
+  if (xs) {
+    q4 = t.get(a.ps_in[4] + so, t.gz, t.gx, xq);
+    axi = t.tabx(a.axi);
+    if (!kFluid) {
+      q7 = t.get(a.ps_in[7] + so, t.gz, t.gx, xq);
+      axh = t.tabx(a.axh);
+    }
+  }
+  if (zs) {
+    q5 = t.get(a.ps_in[5] + so, t.gz, t.gx, zq);
+    azi = t.tabz(a.azi, t.gz);
+    if (!kFluid) {
+      q6 = t.get(a.ps_in[6] + so, t.gz, t.gx, zq);
+      azh = t.tabz(a.azh, t.gz);
+    }
+  }
+  // the shot's receivers in the tile's rows (all of them where there are too few
+  // for a directory)
+  const int4* const rs = a.rec_sorted + (size_t)t.shot * a.nrec;
+  const int e0 = a.rec_dir ? rs[t.z0 / kElTZ].w : 0;
+  const int e1 = a.rec_dir ? rs[t.z0 / kElTZ + 1].w : a.nrec;
+
+  // the halo's planes: rows ezz (czz_z = cxx_x there) and Dz vx, columns exx, Dx vz
+  if (role == 0) {
+    put4(sbf + lr * kTX + t.c, adj_in(ha0.x, hq0, dt * fma_(hc1, hs0, hc0 * hs1)));
+    if (!kFluid) put4(sbg + lr * kTX + t.c, adj_in(ha1.x, hq1, dt * hc2 * hs2));
+  } else if (hc) {
+    const f4 he = adj_in(ha0, hq0, dt * fma_(hc0, hs0, hc1 * hs1));
+    put2(sbe + lr * kElXP + lc, f2{he.x, he.y});
+    if (!kFluid) {
+      const f4 hh = adj_in(ha1, hq1, dt * hc2 * hs2);
+      put2(sbh + lr * kElXP + lc, f2{hh.x, hh.y});
+    }
+  }
+  const f4 ex = dt * fma_(cxx_x, txx, cxx_z * tzz);
+  const f4 ez = dt * fma_(cxx_z, txx, czz_z(a, t.gz, cxx_x) * tzz);
+  const f4 exz = dt * mxz * txz;
+  const f4 be = adj_in(axi, q4, ex), bf = adj_in(azi, q5, ez);
+  const f4 bg = adj_in(azh, q6, exz), bh = adj_in(axh, q7, exz);
+  float* const oe = sbe + t.r * kElXP + 4 + t.c;
+  float* const of = sbf + (t.r + 2) * kTX + t.c;
+  float* const og = sbg + (t.r + 2) * kTX + t.c;
+  float* const oh = sbh + t.r * kElXP + 4 + t.c;
+  put4(oe, be);
+  put4(of, bf);
+  if (!kFluid) {
+    put4(og, bg);
+    put4(oh, bh);
+  }
+  // memory-variable adjoints
+  if (xs) {
+    adj_psi(t, a.ps_out[4] + so, xs, xq, axi, t.tabx(a.bxi), q4, ex);
+    if (!kFluid) adj_psi(t, a.ps_out[7] + so, xs, xq, axh, t.tabx(a.bxh), q7, exz);
+  }
+  if (zs) {
+    adj_psi(t, a.ps_out[5] + so, zs, zq, azi, t.tabz(a.bzi, t.gz), q5, ez);
+    if (!kFluid) adj_psi(t, a.ps_out[6] + so, zs, zq, azh, t.tabz(a.bzh, t.gz), q6, exz);
+  }
+  const bool gacc = !a.g_init;
+  const f4 ovx = t.own(a.vx + so), ovz = t.own(a.vz + so);
+  const f4 fexx = t.own_nt(a.trc[2] + so), fezz = t.own_nt(a.trc[3] + so);
+  const f4 fexz = kFluid ? kZ4 : t.own_nt(a.trc[4] + so);
+  f4 g0 = kZ4, g1 = kZ4, g2 = kZ4;
+  if (gacc) {
+    g0 = t.own_nt(a.g[0] + so);
+    if (!kFluid) {
+      g1 = t.own_nt(a.g[1] + so);
+      g2 = t.own_nt(a.g[2] + so);
+    }
+  }
+  __syncthreads();
+  const bool fs = a.fs && t.z0 == 0 && t.wave == 0;
+  // Vx += (Dx-)^T gbe + (Dz+ of vx)^T gbg ;  (Dx-)^T = -Dx+
+  // Vz += (Dz- of vz)^T gbf + (Dx+)^T gbh ;  (Dx+)^T = -Dx-
+  // (the exz terms are absent in a fluid)
+  f4 dvx = -XWin(oe, be).plus();
+  f4 dvz = dzT(a, 3, of, bf, fs, t.gz, false);
+  if (!kFluid) {
+    dvx = dvx + dzT(a, 2, og, bg, fs, t.gz, true);
+    dvz = dvz + -XWin(oh, bh).minus();
+  }
+  t.put(a.vx + so, ovx + dvx * ih);
+  t.put(a.vz + so, ovz + dvz * ih);
+
+  // coefficient gradients
+  f4 glam = dt * (txx + tzz) * (fexx + fezz);
+  f4 gmu = 2.0f * dt * fma_(txx, fexx, tzz * fezz);
+  if (fs && t.gz == 0) {
+    // txx += dt M exx with M = 4 mu (lambda + mu) / (lambda + 2 mu)
+    const f4 gM = dt * txx * fexx;
+    glam = gM * t.tabx(a.dM_dl);
+    gmu = gM * t.tabx(a.dM_dm);
+  }
+  // a fluid has no mu partials (the gradient finish weighs them by vs = 0;
+  // their planes stay zero)
+  const f4 gmxz = dt * txz * fexz;
+  g0 = gacc ? g0 + glam : glam;
+  g1 = gacc ? g1 + gmu : gmu;
+  g2 = gacc ? g2 + gmxz : gmxz;
+  t.put_nt(a.g[0] + so, g0);
+  if (!kFluid) {
+    t.put_nt(a.g[1] + so, g1);
+    t.put_nt(a.g[2] + so, g2);
+  }
+
+  // residual injection into the velocity adjoints just written (receivers sorted
+  // by (cell, r); the first of each run of equal cells adds the whole run in order)
+  if (e1 > e0) {
+    __syncthreads();
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
+      const int cell = rs[e].y, z = cell / t.NX, x = cell - z * t.NX;
+      if ((unsigned)(x - t.x0) >= (unsigned)kTX || (unsigned)(z - t.z0) >= (unsigned)kElTZ ||
+          (e > e0 && rs[e - 1].y == cell))
+        continue;
+      float ax = a.vx[so + cell], az = a.vz[so + cell];
+      for (int q = e; q < e1 && rs[q].y == cell; ++q) {
+        const float* s = a.resid + (((size_t)t.shot * a.nt + a.n) * a.nrec + rs[q].z) * 2;
+        ax += s[0];
+        az += s[1];
+      }
+      a.vx[so + cell] = ax;
+      a.vz[so + cell] = az;
+    }
+  }
+}
+
+template <int kCols, bool kFluid>
+__global__ __launch_bounds__(kThreads) void el_adj_s_kernel(ElStep a) {
+  __shared__ __attribute__((aligned(16))) float sb[(kFluid ? 1 : 2) * (kAdjX + kAdjZ)];
+  const int f = xcd_spread(blockIdx.x, gridDim.x);
+  EL_DISPATCH(el_adj_s);
+}
+
+// Stress adjoints from the velocity adjoints, buoyancy gradients. Derivative-
+// input adjoints of the velocity step: gba (Dx txx of vx), gbb (Dz txz of vx),
+// gbc (Dx txz of vz), gbd (Dz tzz of vz); a fluid has gba and gbd only.
+template <int kCols, bool kFull, bool kFluid>
+__device__ __forceinline__ void el_adj_v(const ElStep& a, const Tile<kCols, kFull>& t, float* sb) {
+  float* const sba = sb;           // x halo
+  float* const sbd = sb + kAdjX;   // z halo
+  float* const sbb = sbd + kAdjZ;  // z halo
+  float* const sbc = sbb + kAdjZ;  // x halo
+  const size_t so = t.so;
+  const float dt = a.dt, ih = a.ih;
+  const int role = t.role();
+  const bool xs = t.xs();
+  f4 hvx = kZ4, hvz = kZ4, hbx = kZ4, hbz = kZ4, hq0 = kZ4, hq1 = kZ4, ha0 = kZ4, ha1 = kZ4;
+  int hz, hx, lr, lc = 0;
+  bool hc = false;
+  if (role == 0) {  // gbd, gbb
+    t.row_item(hz, lr);
+    hvz = t.get(a.vz + so, hz, t.gx);
+    hbz = t.get(a.bz, hz, t.gx);
+    if (!kFluid) {
+      hvx = t.get(a.vx + so, hz, t.gx);
+      hbx = t.get(a.bx, hz, t.gx);
+    }
+    if (t.zs(t.z0 - 2, 2) || t.zs(t.z0 + kElTZ, 2)) {
+      const bool q = t.zs(hz, 1);
+      hq0 = t.get(a.ps_in[3] + so, hz, t.gx, q);
+      ha0.x = t.tabz(a.azh, hz);
+      if (!kFluid) {
+        hq1 = t.get(a.ps_in[1] + so, hz, t.gx, q);
+        ha1.x = t.tabz(a.azi, hz);
+      }
+    }
+  } else if (role == 1) {  // gba, gbc
+    hc = t.col_item(hz, hx, lr, lc);
+    auto two = [&](const float* f, bool q) {
+      const f2 v = t.part(f, hz, hx, hc && q);
+      return f4{v.x, v.y, 0.0f, 0.0f};
+    };
+    hvx = two(a.vx + so, true);
+    hbx = two(a.bx, true);
+    if (!kFluid) {
+      hvz = two(a.vz + so, true);
+      hbz = two(a.bz, true);
+    }
+    if (xs) {
+      const bool q = t.xq(hx, 2);
+      const f2 u = t.part(a.axh, 0, hx, hc);
+      hq0 = two(a.ps_in[0] + so, q);
+      ha0 = f4{u.x, u.y, 0.0f, 0.0f};
+      if (!kFluid) {
+        const f2 w = t.part(a.axi, 0, hx, hc);
+        hq1 = two(a.ps_in[2] + so, q);
+        ha1 = f4{w.x, w.y, 0.0f, 0.0f};
+      }
+    }
+  }
+  const f4 vx = t.own(a.vx + so), vz = t.own(a.vz + so), bx = t.own(a.bx), bz = t.own(a.bz);
+  const bool zs = t.zs(t.z0 + t.wave * 4, 4);
+  const bool xq = t.xq(t.gx, 4), zq = t.zs(t.gz, 1);
+  f4 axh = kZ4, axi = kZ4, q0 = kZ4, q1 = kZ4, q2 = kZ4, q3 = kZ4;
+  float azi = 0.0f, azh = 0.0f;
+  if (xs) {
+    q0 = t.get(a.ps_in[0] + so, t.gz, t.gx, xq);
+    axh = t.tabx(a.axh);
+    if (!kFluid) {
+      q2 = t.get(a.ps_in[2] + so, t.gz, t.gx, xq);
+      axi = t.tabx(a.axi);
+    }
+  }
+  if (zs) {
+    q3 = t.get(a.ps_in[3] + so, t.gz, t.gx, zq);
+    azh = t.tabz(a.azh, t.gz);
+    if (!kFluid) {
+      q1 = t.get(a.ps_in[1] + so, t.gz, t.gx, zq);
+      azi = t.tabz(a.azi, t.gz);
+    }
+  }
+  if (role == 0) {
+    put4(sbd + lr * kTX + t.c, adj_in(ha0.x, hq0, dt * hbz * hvz));
+    if (!kFluid) put4(sbb + lr * kTX + t.c, adj_in(ha1.x, hq1, dt * hbx * hvx));
+  } else if (hc) {
+    const f4 h0 = adj_in(ha0, hq0, dt * hbx * hvx);
+    put2(sba + lr * kElXP + lc, f2{h0.x, h0.y});
+    if (!kFluid) {
+      const f4 h2 = adj_in(ha1, hq1, dt * hbz * hvz);
+      put2(sbc + lr * kElXP + lc, f2{h2.x, h2.y});
+    }
+  }
+  const f4 kx = dt * bx * vx, kz = dt * bz * vz;
+  const f4 ba = adj_in(axh, q0, kx), bb = adj_in(azi, q1, kx);
+  const f4 bc = adj_in(axi, q2, kz), bd = adj_in(azh, q3, kz);
+  float* const oa = sba + t.r * kElXP + 4 + t.c;
+  float* const od = sbd + (t.r + 2) * kTX + t.c;
+  float* const ob = sbb + (t.r + 2) * kTX + t.c;
+  float* const oc = sbc + t.r * kElXP + 4 + t.c;
+  put4(oa, ba);
+  put4(od, bd);
+  if (!kFluid) {
+    put4(ob, bb);
+    put4(oc, bc);
+  }
+  if (xs) {
+    adj_psi(t, a.ps_out[0] + so, xs, xq, axh, t.tabx(a.bxh), q0, kx);
+    if (!kFluid) adj_psi(t, a.ps_out[2] + so, xs, xq, axi, t.tabx(a.bxi), q2, kz);
+  }
+  if (zs) {
+    adj_psi(t, a.ps_out[3] + so, zs, zq, azh, t.tabz(a.bzh, t.gz), q3, kz);
+    if (!kFluid) adj_psi(t, a.ps_out[1] + so, zs, zq, azi, t.tabz(a.bzi, t.gz), q1, kx);
+  }
+  const bool gacc = !a.g_init;
+  const f4 otxx = t.own(a.txx + so), otzz = t.own(a.tzz + so);
+  const f4 otxz = kFluid ? kZ4 : t.own(a.txz + so);
+  const f4 f0 = t.own_nt(a.trc[0] + so), f1 = t.own_nt(a.trc[1] + so);
+  f4 g3 = kZ4, g4 = kZ4;
+  if (gacc) {
+    g3 = t.own_nt(a.g[3] + so);
+    g4 = t.own_nt(a.g[4] + so);
+  }
+  __syncthreads();
+  const bool fs = a.fs && t.z0 == 0 && t.wave == 0;
+  // Txx += (Dx+)^T gba = -Dx- gba ;  Tzz += (Dz+ of tzz)^T gbd
+  t.put(a.txx + so, otxx + -XWin(oa, ba).minus() * ih);
+  t.put(a.tzz + so, otzz + dzT(a, 0, od, bd, fs, t.gz, true) * ih);
+  // Txz += (Dz- of txz)^T gbb + (Dx-)^T gbc = ... - Dx+ gbc (a fluid's txz
+  // adjoint reaches nothing: its only use is weighed by mu = 0)
+  if (!kFluid)
+    t.put(a.txz + so, otxz + (dzT(a, 1, ob, bb, fs, t.gz, false) + -XWin(oc, bc).plus()) * ih);
+
+  const f4 gbx = dt * vx * f0, gbz = dt * vz * f1;
+  g3 = gacc ? g3 + gbx : gbx;
+  g4 = gacc ? g4 + gbz : gbz;
+  t.put_nt(a.g[3] + so, g3);
+  t.put_nt(a.g[4] + so, g4);
+}
+
+template <int kCols, bool kFluid>
+__global__ __launch_bounds__(kThreads) void el_adj_v_kernel(ElStep a) {
+  __shared__ __attribute__((aligned(16))) float sb[(kFluid ? 1 : 2) * (kAdjX + kAdjZ)];
+  const int f = xcd_spread(blockIdx.x, gridDim.x);
+  EL_DISPATCH(el_adj_v);
 }
 
 // ---------------------------------------------------------------------------
@@ -890,8 +1101,41 @@ __global__ __launch_bounds__(256) void el_finish_kernel(const double* tot, ElCoe
   }
 }
 
-dim3 grid_of(const ElStep& a) {
-  return dim3(((a.NX + kTX - 1) / kTX) * ((a.NZ + kElTZ - 1) / kElTZ) * a.nshots);
+int tiles_of(const ElStep& a) {
+  return ((a.NX + kTX - 1) / kTX) * ((a.NZ + kElTZ - 1) / kElTZ) * a.nshots;
+}
+
+template <int kCols, bool kFluid>
+void launch_fwd(const ElStep& a, hipStream_t s) {
+  const int n = tiles_of(a);
+  const int rec = a.gathers ? (int)(((size_t)a.nshots * a.nrec + kThreads - 1) / kThreads) : 0;
+  hipLaunchKernelGGL((el_vel_kernel<kCols, kFluid>), dim3(n), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL((el_str_kernel<kCols, kFluid>), dim3(n + rec), dim3(kThreads), 0, s, a, n);
+}
+template <int kCols, bool kFluid>
+void launch_adj(const ElStep& a, hipStream_t s) {
+  const int n = tiles_of(a);
+  hipLaunchKernelGGL((el_adj_s_kernel<kCols, kFluid>), dim3(n), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL((el_adj_v_kernel<kCols, kFluid>), dim3(n), dim3(kThreads), 0, s, a);
+}
+template <int kCols>
+void launch(const ElStep& a, bool adj, hipStream_t s) {
+  if (adj)
+    a.fluid ? launch_adj<kCols, true>(a, s) : launch_adj<kCols, false>(a, s);
+  else
+    a.fluid ? launch_fwd<kCols, true>(a, s) : launch_fwd<kCols, false>(a, s);
+}
+int launch(const ElStep& a, bool adj, hipStream_t s, hipEvent_t* ev) {
+  if (ev) SWEEP_HIP(hipEventRecord(ev[0], s));
+  if (a.NX % 4 == 0)
+    launch<4>(a, adj, s);
+  else if (a.NX % 2 == 0)
+    launch<2>(a, adj, s);
+  else
+    launch<1>(a, adj, s);
+  if (ev) SWEEP_HIP(hipEventRecord(ev[1], s));
+  SWEEP_HIP(hipGetLastError());
+  return SWEEP_OK;
 }
 
 }  // namespace
@@ -911,41 +1155,9 @@ int el_launch_prep(const float* model, const ElCoef& c, int nx, int nz, int P, i
   return SWEEP_OK;
 }
 
-int el_launch_fwd(const ElStep& a, hipStream_t s, hipEvent_t* ev) {
-  if (ev) SWEEP_HIP(hipEventRecord(ev[0], s));
-  if (a.fluid)
-    hipLaunchKernelGGL(el_vel_kernel<true>, grid_of(a), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(el_vel_kernel<false>, grid_of(a), dim3(256), 0, s, a);
-  if (a.gathers && a.nrec > 0)
-    hipLaunchKernelGGL(el_record_kernel, dim3((a.nshots * a.nrec + 255) / 256), dim3(256), 0, s,
-                       a);
-  if (a.fluid)
-    hipLaunchKernelGGL(el_str_kernel<true>, grid_of(a), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(el_str_kernel<false>, grid_of(a), dim3(256), 0, s, a);
-  if (ev) SWEEP_HIP(hipEventRecord(ev[1], s));
-  SWEEP_HIP(hipGetLastError());
-  return SWEEP_OK;
-}
+int el_launch_fwd(const ElStep& a, hipStream_t s, hipEvent_t* ev) { return launch(a, false, s, ev); }
 
-int el_launch_adj(const ElStep& a, hipStream_t s, hipEvent_t* ev) {
-  if (ev) SWEEP_HIP(hipEventRecord(ev[0], s));
-  if (a.fluid)
-    hipLaunchKernelGGL(el_adj_s_kernel<true>, grid_of(a), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(el_adj_s_kernel<false>, grid_of(a), dim3(256), 0, s, a);
-  if (a.nrec > 0)
-    hipLaunchKernelGGL(el_inject_kernel, dim3((a.nshots * a.nrec + 255) / 256), dim3(256), 0, s,
-                       a, a.n);
-  if (a.fluid)
-    hipLaunchKernelGGL(el_adj_v_kernel<true>, grid_of(a), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(el_adj_v_kernel<false>, grid_of(a), dim3(256), 0, s, a);
-  if (ev) SWEEP_HIP(hipEventRecord(ev[1], s));
-  SWEEP_HIP(hipGetLastError());
-  return SWEEP_OK;
-}
+int el_launch_adj(const ElStep& a, hipStream_t s, hipEvent_t* ev) { return launch(a, true, s, ev); }
 
 int el_launch_fold(double* tot, const float* gpart, int nshots, size_t plane, hipStream_t s) {
   hipLaunchKernelGGL(el_fold_kernel, dim3((unsigned)((plane + 255) / 256), 5), dim3(256), 0, s,

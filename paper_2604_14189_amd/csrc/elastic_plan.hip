@@ -72,6 +72,33 @@ int fwd_taps(int kind, int j, int* off, float* w) {
 
 }  // namespace
 
+// The receivers of the elastic reverse step sorted by (shot, cell, r), with a
+// directory over the tile rows in the spare word of each shot's first entries
+// where there are enough of them.
+static int el_rec_dir(const sweep_plan* p) {
+  return p->pb.nrec >= (p->NZ + kElTileRows - 1) / kElTileRows + 1;
+}
+void el_build_receivers(sweep_plan* p) {
+  const int nrec = p->pb.nrec;
+  p->rec_sorted.resize(p->rec_cell.size());
+  for (size_t r = 0; r < p->rec_cell.size(); ++r)
+    p->rec_sorted[r] = make_int4((int)(r / nrec), p->rec_cell[r], (int)(r % nrec), 0);
+  std::sort(p->rec_sorted.begin(), p->rec_sorted.end(), [](const int4& a, const int4& b) {
+    if (a.x != b.x) return a.x < b.x;
+    if (a.y != b.y) return a.y < b.y;
+    return a.z < b.z;
+  });
+  if (!el_rec_dir(p)) return;
+  const int rows = (p->NZ + kElTileRows - 1) / kElTileRows;
+  for (int s = 0; s < p->pb.nshots; ++s) {
+    int4* e = p->rec_sorted.data() + (size_t)s * nrec;
+    for (int k = 0, q = 0; k <= rows; ++k) {
+      while (q < nrec && e[q].y / p->NX / kElTileRows < k) ++q;
+      e[k].w = q;
+    }
+  }
+}
+
 // Transposed taps for input rows 0..3: (D^T g)[jin] = sum_jout w(jout, jin) g[jout],
 // collected from every output row whose forward taps reach jin.
 void el_build_tables(sweep_plan* p) {
@@ -170,6 +197,8 @@ ElStep step_base(const sweep_plan* p, void* work, const ElLayout& L, const ElCoe
   a.nrec = p->pb.nrec;
   a.nshots = p->pb.nshots;
   a.fs = p->pb.free_surface;
+  a.P = p->P;
+  a.top = a.fs ? 0 : p->P;
   a.fluid = p->pb.physics == SWEEP_ACOUSTIC_VD;
   a.dt = (float)p->pb.dt;
   a.w = (float)(p->pb.dt / (p->pb.h * p->pb.h));
@@ -194,6 +223,7 @@ ElStep step_base(const sweep_plan* p, void* work, const ElLayout& L, const ElCoe
   a.wavelet = at<float>(work, L.wav);
   a.rec_cell = at<int>(work, L.rec_cell);
   a.rec_sorted = at<int4>(work, L.rec_sorted);
+  a.rec_dir = el_rec_dir(p);
   std::memcpy(a.tt_cnt, p->tt_cnt, sizeof(a.tt_cnt));
   std::memcpy(a.tt_off, p->tt_off, sizeof(a.tt_off));
   std::memcpy(a.tt_w, p->tt_w, sizeof(a.tt_w));

@@ -158,8 +158,8 @@ struct sweep_plan {
   // alone or for the batch it runs in)
   bool whole = false;
   sweep::Rot frot, arot;  // forward / adjoint buffer rotation
-  // elastic: receivers sorted by (shot, cell, r) for deterministic injection,
-  // and the transposed z-taps of the first rows under a free surface
+  // elastic: receivers sorted by (shot, cell, r) for deterministic injection
+  // (with a directory over tile rows), and the transposed z-taps of the first rows under a free surface
   std::vector<int4> rec_sorted;
   int tt_cnt[4][4];
   int tt_off[4][4][8];
@@ -186,6 +186,7 @@ void ac_build_tiling(sweep_plan* p);
 void ac_layout(const sweep_plan* p, AcLayout& L, bool keep = true);
 void el_layout(const sweep_plan* p, ElLayout& L);
 void el_build_tables(sweep_plan* p);
+void el_build_receivers(sweep_plan* p);
 // Forward and backward of the staggered (elastic, variable-density) and VTI
 // plans. Each is also split for graph capture: *_prepare / *_backward_check
 // (workspace checks and host-to-device geometry copies, not captured), then
