@@ -32,6 +32,34 @@ __device__ __forceinline__ bool in_grid(int gx, int gz, int NX, int NZ) {
   return gx >= 0 && gx < NX && gz >= 0 && gz < NZ;
 }
 
+// Guarded load: every lane loads, from index 0 where !ok, and the value is
+// selected afterwards (a branch would wait for each load in turn).
+template <class T>
+__device__ __forceinline__ T ldsel(const T* f, unsigned i, bool ok) {
+  const T v = u32at(f, ok ? i : 0u);
+  return ok ? v : T(0);
+}
+
+// Own cells of a field, with the non-temporal hint (kNt) or without. With it a
+// field does not stay in the last-level cache from step to step.
+template <bool kNt, class T>
+__device__ __forceinline__ T ld_field(const T* p) {
+  return kNt ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool kNt, class T>
+__device__ __forceinline__ void st_field(T* p, T v) {
+  if (kNt)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+template <bool kNt, class T>
+__device__ __forceinline__ T ldsel_field(const T* f, unsigned i, bool ok) {
+  const T v = ld_field<kNt>(&u32at(f, ok ? i : 0u));
+  return ok ? v : T(0);
+}
+
 // Stage field f on the box [x0 - hx, x0 + 64 + hx) x [z0 - hz, z0 + 16 + hz)
 // of W x H cells, zero outside the grid; all loads of a lane first, then its
 // LDS stores.
@@ -47,7 +75,7 @@ __device__ __forceinline__ void stage(T* s, const T* __restrict__ f, int x0, int
     const int r = e / W, c = e - r * W;
     const int gx = x0 - hx + c, gz = z0 - hz + r;
     const bool ok = e < N && in_grid(gx, gz, NX, NZ);
-    v[k] = ok ? u32at(f, (unsigned)(gz * NX + gx)) : T(0);
+    v[k] = ldsel(f, (unsigned)(gz * NX + gx), ok);
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -80,7 +108,7 @@ __device__ __forceinline__ void stage_split(float* hi, unsigned short* lo,
     const int r = e / W, c = e - r * W;
     const int gx = x0 - hx + c, gz = z0 - hz + r;
     const bool ok = e < N && in_grid(gx, gz, NX, NZ);
-    v[k] = ok ? u32at(f, (unsigned)(gz * NX + gx)) : 0.0;
+    v[k] = ldsel(f, (unsigned)(gz * NX + gx), ok);
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -122,6 +150,7 @@ __device__ __forceinline__ void vti_record(const VtiStep& a, int shot, int tile,
   }
 }
 
+template <bool kNt>
 __global__ __launch_bounds__(kThreads) void vti_fwd_kernel(VtiStep a) {
   __shared__ float sP[PH * PW];            // P^n: hi, 8-cell halo
   __shared__ unsigned short sPl[PH * PW];  // and lo
@@ -153,8 +182,8 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_kernel(VtiStep a) {
     const bool ok = gx < NX && gz < NZ;
     const unsigned idx = ok ? (unsigned)(gz * NX + gx) : 0u;
     pown[r] = ok ? u32at(a.pcur + base, idx) : 0.0;
-    pold[r] = ok ? __builtin_nontemporal_load(&u32at(a.pprev + base, idx)) : 0.0;
-    gold[r] = ok ? __builtin_nontemporal_load(&u32at(a.gprev + base, idx)) : 0.0;
+    pold[r] = ok ? ld_field<kNt>(&u32at(a.pprev + base, idx)) : 0.0;
+    gold[r] = ok ? ld_field<kNt>(&u32at(a.gprev + base, idx)) : 0.0;
     ccx[r] = ok ? u32at(a.cx, idx) : 0.0f;
     ccz[r] = ok ? u32at(a.cz, idx) : 0.0f;
     ccm[r] = ok ? u32at(a.cm, idx) : 0.0f;
@@ -246,8 +275,8 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_kernel(VtiStep a) {
     const double gn = (2.0 * g0[rr] - gold[rr]) + p0;
     out[rr] = (float)pn;
     if (ok) {
-      __builtin_nontemporal_store(pn, &u32at(a.pprev + base, idx));
-      __builtin_nontemporal_store(gn, &u32at(a.gprev + base, idx));
+      st_field<kNt>(&u32at(a.pprev + base, idx), pn);
+      st_field<kNt>(&u32at(a.gprev + base, idx), gn);
       if (a.tr[0]) {
         st_nt(&u32at(a.tr[0] + base, idx), bxv);
         st_nt(&u32at(a.tr[1] + base, idx), bzv);
@@ -273,6 +302,7 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_kernel(VtiStep a) {
 //   mu^n     = 2 mu^{n+1} - mu^{n+2} - D2x' D2z' (cm P1),
 // Psi = b psbar, Z = b (Z + q); g += P1 (Bx', Bz', -D2x'D2z'G^n); then r_{n-1}
 // is added at the receivers.
+template <bool kNt>
 __global__ __launch_bounds__(kThreads) void vti_adj_kernel(VtiStep a) {
   // lambda^{n+1} with an 8-cell halo; once the products are formed, the same
   // memory holds D2z'(cm lambda^{n+1}) (float64, tile rows, 4-column ring),
@@ -303,9 +333,9 @@ __global__ __launch_bounds__(kThreads) void vti_adj_kernel(VtiStep a) {
     const int gz = z0 + zb + r;
     const bool ok = gx < NX && gz < NZ;
     const unsigned idx = ok ? (unsigned)(gz * NX + gx) : 0u;
-    l2[r] = ok ? ld_nt(&u32at(a.prev + base, idx)) : 0.0f;
+    l2[r] = ok ? ld_field<kNt>(&u32at(a.prev + base, idx)) : 0.0f;
     m1[r] = ok ? u32at(a.mcur + base, idx) : 0.0;
-    m2[r] = ok ? __builtin_nontemporal_load(&u32at(a.mprev + base, idx)) : 0.0;
+    m2[r] = ok ? ld_field<kNt>(&u32at(a.mprev + base, idx)) : 0.0;
     ccx[r] = ok ? u32at(a.cx, idx) : 0.0f;
     ccz[r] = ok ? u32at(a.cz, idx) : 0.0f;
     t0[r] = ok ? ld_nt(&u32at(a.trc[0] + base, idx)) : 0.0f;
@@ -437,7 +467,7 @@ __global__ __launch_bounds__(kThreads) void vti_adj_kernel(VtiStep a) {
     const int zrow = zstrip_row(gz, NZ, P);
     if (zrow >= 0)
       u32at(a.zez_out + (size_t)shot * P2 * NX, (unsigned)(zrow * NX + gx)) = a.bz[gz] * (zz[rr] + ccz[rr] * l1);
-    __builtin_nontemporal_store(mu, &u32at(a.mprev + base, idx));
+    st_field<kNt>(&u32at(a.mprev + base, idx), mu);
     float* g0 = &u32at(a.g + base, idx);
     float* g1 = &u32at(a.g + base + (size_t)a.nshots * plane, idx);
     float* g2 = &u32at(a.g + base + 2 * (size_t)a.nshots * plane, idx);
@@ -476,7 +506,7 @@ __global__ __launch_bounds__(kThreads) void vti_adj_kernel(VtiStep a) {
 #pragma unroll
   for (int rr = 0; rr < kRZ; ++rr) {
     const int gz = z0 + zb + rr;
-    if (gx < NX && gz < NZ) st_nt(&u32at(a.prev + base, (unsigned)(gz * NX + gx)), out[rr]);
+    if (gx < NX && gz < NZ) st_field<kNt>(&u32at(a.prev + base, (unsigned)(gz * NX + gx)), out[rr]);
   }
 }
 
@@ -484,7 +514,13 @@ __global__ __launch_bounds__(kThreads) void vti_adj_kernel(VtiStep a) {
 // term of the general kernels is an exact zero there and the rings that carry
 // them are not needed. The same operations on the same values (so the same
 // bits), with P^n staged with a 4-cell halo: about half the LDS of the
-// general kernels and fewer registers, for more work-groups per CU.
+// general kernels and fewer registers, for more work-groups per CU. Their guarded
+// loads are selects, and the reverse kernel has the gradient partials in flight
+// over the stencils: written as branches and read at the end, the loads of a lane
+// waited for each other (1080 x 380 cells, 16 shots: 54 -> 45 us forward, 87 -> 65
+// us in reverse). In the general kernels the same costs more registers than it
+// gives (46 -> 50 us, 93 -> 103 us), so they keep the branches.
+template <bool kNt>
 __global__ __launch_bounds__(kThreads) void vti_fwd_int_kernel(VtiStep a) {
   __shared__ float sP[GH * GW];            // P^n: hi, 4-cell halo
   __shared__ unsigned short sPl[GH * GW];  // and lo
@@ -506,12 +542,12 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_int_kernel(VtiStep a) {
     const int gz = z0 + zb + r;
     const bool ok = gx < NX && gz < NZ;
     const unsigned idx = ok ? (unsigned)(gz * NX + gx) : 0u;
-    pown[r] = ok ? u32at(a.pcur + base, idx) : 0.0;
-    pold[r] = ok ? __builtin_nontemporal_load(&u32at(a.pprev + base, idx)) : 0.0;
-    gold[r] = ok ? __builtin_nontemporal_load(&u32at(a.gprev + base, idx)) : 0.0;
-    ccx[r] = ok ? u32at(a.cx, idx) : 0.0f;
-    ccz[r] = ok ? u32at(a.cz, idx) : 0.0f;
-    ccm[r] = ok ? u32at(a.cm, idx) : 0.0f;
+    pown[r] = ldsel(a.pcur + base, idx, ok);
+    pold[r] = ldsel_field<kNt>(a.pprev + base, idx, ok);
+    gold[r] = ldsel_field<kNt>(a.gprev + base, idx, ok);
+    ccx[r] = ldsel(a.cx, idx, ok);
+    ccz[r] = ldsel(a.cz, idx, ok);
+    ccm[r] = ldsel(a.cm, idx, ok);
   }
   stage_split<GW, GH>(sP, sPl, a.pcur + base, x0, z0, 4, 4, NX, NZ);
   stage<GW, GH>(sG, a.gcur + base, x0, z0, 4, 4, NX, NZ);
@@ -553,8 +589,8 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_int_kernel(VtiStep a) {
     const double gn = (2.0 * g0[rr] - gold[rr]) + p0;
     out[rr] = (float)pn;
     if (ok) {
-      __builtin_nontemporal_store(pn, &u32at(a.pprev + base, idx));
-      __builtin_nontemporal_store(gn, &u32at(a.gprev + base, idx));
+      st_field<kNt>(&u32at(a.pprev + base, idx), pn);
+      st_field<kNt>(&u32at(a.gprev + base, idx), gn);
       if (a.tr[0]) {
         st_nt(&u32at(a.tr[0] + base, idx), bxv);
         st_nt(&u32at(a.tr[1] + base, idx), bzv);
@@ -572,6 +608,7 @@ __global__ __launch_bounds__(kThreads) void vti_fwd_int_kernel(VtiStep a) {
   }
 }
 
+template <bool kNt>
 __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
   __shared__ float sQx[kTZ * GW];  // cx lambda^{n+1} on the tile rows, 4-column ring
   __shared__ float sQz[GH * kTX];  // cz lambda^{n+1} on the tile columns, 4-row ring
@@ -597,10 +634,10 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
     const int x = x0 - 4 + c, z = z0 - 4 + r;
     const bool ok = e < NB && in_grid(x, z, NX, NZ);
     const unsigned idx = ok ? (unsigned)(z * NX + x) : 0u;
-    bl[k] = ok ? u32at(a.cur + base, idx) : 0.0f;
-    bcx[k] = ok ? u32at(a.cx, idx) : 0.0f;
-    bcz[k] = ok ? u32at(a.cz, idx) : 0.0f;
-    bcm[k] = ok ? u32at(a.cm, idx) : 0.0f;
+    bl[k] = ldsel(a.cur + base, idx, ok);
+    bcx[k] = ldsel(a.cx, idx, ok);
+    bcz[k] = ldsel(a.cz, idx, ok);
+    bcm[k] = ldsel(a.cm, idx, ok);
   }
   float l1v[kRZ], l2[kRZ], t0[kRZ], t1[kRZ], t2[kRZ];
   double m1[kRZ], m2[kRZ];
@@ -609,13 +646,13 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
     const int gz = z0 + zb + r;
     const bool ok = gx < NX && gz < NZ;
     const unsigned idx = ok ? (unsigned)(gz * NX + gx) : 0u;
-    l1v[r] = ok ? u32at(a.cur + base, idx) : 0.0f;
-    l2[r] = ok ? ld_nt(&u32at(a.prev + base, idx)) : 0.0f;
-    m1[r] = ok ? u32at(a.mcur + base, idx) : 0.0;
-    m2[r] = ok ? __builtin_nontemporal_load(&u32at(a.mprev + base, idx)) : 0.0;
-    t0[r] = ok ? ld_nt(&u32at(a.trc[0] + base, idx)) : 0.0f;
-    t1[r] = ok ? ld_nt(&u32at(a.trc[1] + base, idx)) : 0.0f;
-    t2[r] = ok ? ld_nt(&u32at(a.trc[2] + base, idx)) : 0.0f;
+    l1v[r] = ldsel(a.cur + base, idx, ok);
+    l2[r] = ldsel_field<kNt>(a.prev + base, idx, ok);
+    m1[r] = ldsel(a.mcur + base, idx, ok);
+    m2[r] = ldsel_field<kNt>(a.mprev + base, idx, ok);
+    t0[r] = ldz32_nt(a.trc[0] + base, idx, ok);
+    t1[r] = ldz32_nt(a.trc[1] + base, idx, ok);
+    t2[r] = ldz32_nt(a.trc[2] + base, idx, ok);
   }
   // products (outside the grid every operand is 0)
 #pragma unroll
@@ -625,6 +662,22 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
     if (r >= 4 && r < 4 + kTZ) sQx[(r - 4) * GW + c] = bcx[k] * bl[k];
     if (c >= 4 && c < 4 + kTX) sQz[r * kTX + c - 4] = bcz[k] * bl[k];
     sM[e] = (double)bcm[k] * (double)bl[k];
+  }
+  // the gradient partials, in flight over the stencils
+  const float* const gp = a.g + base;
+  const size_t gq = (size_t)a.nshots * plane;
+  float ga[kRZ], gb[kRZ], gc[kRZ];
+#pragma unroll
+  for (int r = 0; r < kRZ; ++r) {
+    const int gz = z0 + zb + r;
+    const bool ok = gx < NX && gz < NZ && !a.g_init;
+    const unsigned idx = ok ? (unsigned)(gz * NX + gx) : 0u;
+    ga[r] = gb[r] = gc[r] = 0.0f;
+    if (!a.g_init) {
+      ga[r] = ldz32_nt(gp, idx, ok);
+      gb[r] = ldz32_nt(gp + gq, idx, ok);
+      gc[r] = ldz32_nt(gp + 2 * gq, idx, ok);
+    }
   }
   __syncthreads();
   constexpr int KT = (kTZ * GW + kThreads - 1) / kThreads;
@@ -656,7 +709,7 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
     const double mu = (2.0 * m1[rr] - m2[rr]) - d2d(&sU[r * GW + lx + 4], 1);
     out[rr] = lam;
     if (!ok) continue;
-    __builtin_nontemporal_store(mu, &u32at(a.mprev + base, idx));
+    st_field<kNt>(&u32at(a.mprev + base, idx), mu);
     float* g0 = &u32at(a.g + base, idx);
     float* g1 = &u32at(a.g + base + (size_t)a.nshots * plane, idx);
     float* g2 = &u32at(a.g + base + 2 * (size_t)a.nshots * plane, idx);
@@ -665,9 +718,9 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
       st_nt(g1, l1 * t1[rr]);
       st_nt(g2, -(l1 * t2[rr]));
     } else {
-      st_nt(g0, fmaf(l1, t0[rr], ld_nt(g0)));
-      st_nt(g1, fmaf(l1, t1[rr], ld_nt(g1)));
-      st_nt(g2, ld_nt(g2) - l1 * t2[rr]);
+      st_nt(g0, fmaf(l1, t0[rr], ga[rr]));
+      st_nt(g1, fmaf(l1, t1[rr], gb[rr]));
+      st_nt(g2, gc[rr] - l1 * t2[rr]);
     }
   }
   // r_{n-1} at the receivers of this (shot, tile), as in vti_adj_kernel
@@ -695,7 +748,7 @@ __global__ __launch_bounds__(kThreads) void vti_adj_int_kernel(VtiStep a) {
 #pragma unroll
   for (int rr = 0; rr < kRZ; ++rr) {
     const int gz = z0 + zb + rr;
-    if (gx < NX && gz < NZ) st_nt(&u32at(a.prev + base, (unsigned)(gz * NX + gx)), out[rr]);
+    if (gx < NX && gz < NZ) st_field<kNt>(&u32at(a.prev + base, (unsigned)(gz * NX + gx)), out[rr]);
   }
 }
 
@@ -785,25 +838,42 @@ bool vti_near_strip(int x0, int z0, int NX, int NZ, int P) {
   return P > 0 && (x0 - 4 < P || x0 + kTX + 4 > NX - P || z0 - 4 < P || z0 + kTZ + 4 > NZ - P);
 }
 
+// The kernels hint their fields where P and G, old and new (32 bytes a cell),
+// exceed the last-level cache. 1080 x 380 cells, forward and reverse step, us:
+// 16 shots (210 MB) 115 and 185 with the hint, 101 and 180 without; 32 shots 212
+// and 350 with it, 223 and 364 without.
+static bool vti_hint(const VtiStep& a) {
+  return (size_t)a.nshots * a.NX * a.NZ * 32 > (size_t)240 << 20;
+}
+
 // Within a step every tile reads only the current level around it and writes
 // its own cells of the other buffers, so the two tile sets may run in either
 // order.
-int vti_launch_fwd(const VtiStep& a, hipStream_t s) {
+template <bool kNt>
+static int launch_fwd(const VtiStep& a, hipStream_t s) {
   if (a.n_int > 0)
-    hipLaunchKernelGGL(vti_fwd_int_kernel, dim3(a.n_int * a.nshots), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(vti_fwd_int_kernel<kNt>, dim3(a.n_int * a.nshots), dim3(kThreads), 0, s, a);
   if (a.n_pml > 0)
-    hipLaunchKernelGGL(vti_fwd_kernel, dim3(a.n_pml * a.nshots), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(vti_fwd_kernel<kNt>, dim3(a.n_pml * a.nshots), dim3(kThreads), 0, s, a);
+  SWEEP_HIP(hipGetLastError());
+  return SWEEP_OK;
+}
+template <bool kNt>
+static int launch_adj(const VtiStep& a, hipStream_t s) {
+  if (a.n_int > 0)
+    hipLaunchKernelGGL(vti_adj_int_kernel<kNt>, dim3(a.n_int * a.nshots), dim3(kThreads), 0, s, a);
+  if (a.n_pml > 0)
+    hipLaunchKernelGGL(vti_adj_kernel<kNt>, dim3(a.n_pml * a.nshots), dim3(kThreads), 0, s, a);
   SWEEP_HIP(hipGetLastError());
   return SWEEP_OK;
 }
 
+int vti_launch_fwd(const VtiStep& a, hipStream_t s) {
+  return vti_hint(a) ? launch_fwd<true>(a, s) : launch_fwd<false>(a, s);
+}
+
 int vti_launch_adj(const VtiStep& a, hipStream_t s) {
-  if (a.n_int > 0)
-    hipLaunchKernelGGL(vti_adj_int_kernel, dim3(a.n_int * a.nshots), dim3(kThreads), 0, s, a);
-  if (a.n_pml > 0)
-    hipLaunchKernelGGL(vti_adj_kernel, dim3(a.n_pml * a.nshots), dim3(kThreads), 0, s, a);
-  SWEEP_HIP(hipGetLastError());
-  return SWEEP_OK;
+  return vti_hint(a) ? launch_adj<true>(a, s) : launch_adj<false>(a, s);
 }
 
 int vti_launch_fold(double* tot, const float* gpart, int nshots, size_t plane, hipStream_t s) {
