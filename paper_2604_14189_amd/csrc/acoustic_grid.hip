@@ -1,5 +1,6 @@
 // Acoustic steps over the whole padded grid in one launch, for calls whose
-// steps are too short to fill the chip (the recurrence of acoustic.hip with the
+// steps are too short to fill the chip and whose sizes the four-column items of
+// acoustic_wide.hip do not fit (the recurrence of acoustic.hip with the
 // same operations in the same order, so the same bits).
 //
 // Such a step is bound by latency: of the launches and, in each, of the chain
@@ -612,6 +613,12 @@ int check_grid(const AcStep& a, GridStep kind) {
   return SWEEP_OK;
 }
 
+int check_wide(const AcStep& a) {
+  if (ac_wide_sizes(a.NX, a.P, a.tz)) return SWEEP_OK;
+  set_error("one-launch step of four-column items: sizes not aligned");
+  return SWEEP_EINVAL;
+}
+
 }  // namespace
 
 int ac_launch_grid(const AcStep& a, GridStep kind, hipStream_t s) {
@@ -625,21 +632,24 @@ int ac_launch_grid(const AcStep& a, GridStep kind, hipStream_t s) {
   return SWEEP_OK;
 }
 
-int ac_launch_grid_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s) {
+int ac_launch_grid_batch(const AcStep* steps, int n, GridStep kind, bool wide, hipStream_t s) {
   AcBatch b;
   for (int q = 0; q < n;) {
     b.nplans = 0;
     b.base[0] = 0;
     bool odd = false;
     for (; q < n && b.nplans < kPlansPerLaunch; ++q) {
-      const int rc = check_grid(steps[q], kind);
+      const AcStep& a = steps[q];
+      const int rc = wide ? check_wide(a) : check_grid(a, kind);
       if (rc) return rc;
       const int k = b.nplans++;
       b.step[k] = steps[q];
-      b.base[k + 1] = b.base[k] + grid_blocks(steps[q]);
-      odd = odd || odd_sizes(steps[q]);
+      b.base[k + 1] = b.base[k] + (wide ? grid_blocks(a) / 2 : grid_blocks(a));
+      odd = odd || odd_sizes(a);
     }
-    if (odd)
+    if (wide) {
+      if (const int rc = ac_launch_wide_batch(b, kind, s)) return rc;
+    } else if (odd)
       launch_grid_batch<true>(b, kind, s);
     else
       launch_grid_batch<false>(b, kind, s);

@@ -288,19 +288,94 @@ int check_work(const sweep_plan* p, size_t need, void* work, size_t bytes) {
 size_t ac_cells(const sweep_plan* p) { return (size_t)p->pb.nshots * p->NX * p->NZ; }
 
 // Whether the steps of a call over `cells` padded cells (all shots) take one
-// launch for the whole grid; `adjoint`: the call has adjoint or Born steps.
-// Only under the default tiling, so that a tiling that the caller names is the
-// one that runs. One launch wins while launches and latency bound a step, and
-// beyond that while the fields stay in the 256 MB last-level cache: they take
-// 16 bytes a cell forward and up to 28 with the adjoint's operands. us per step
-// by tile sets / in one launch (1080 x 380 shots): forward 1 shot 21.3 / 6.3,
-// 16 shots (6.6 M cells) 37.2 / 29.9, 32 shots (13.1 M) 61.6 / 54.1, 64 shots
+// launch of two-column items for the whole grid; `adjoint`: the call has adjoint
+// or Born steps. Only under the default tiling, so that a tiling that the caller
+// names is the one that runs. One launch wins while launches and latency bound a
+// step, and beyond that while the fields stay in the 256 MB last-level cache. us
+// per step by tile sets / in one launch (1080 x 380 shots): forward 1 shot 21.3 /
+// 6.3, 16 shots (6.6 M cells) 37.2 / 29.9, 32 shots (13.1 M) 61.6 / 54.1, 64 shots
 // (26 M) 107.7 / 146.4; gradient 1 shot 70.9 / 21.7, 16 shots 140.3 / 114.2, 32
 // shots 238.2 / 239.4; Born 16 shots 87.5 / 69.7, 32 shots 153.0 / 159.8.
 constexpr size_t kWholeForward = 13600000, kWholeAdjoint = 8400000;
+bool ac_default_tiling(const sweep_tuning& t) {
+  return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2;
+}
 bool ac_whole(const sweep_tuning& t, size_t cells, bool adjoint) {
-  return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2 &&
-         cells <= (adjoint ? kWholeAdjoint : kWholeForward);
+  return ac_default_tiling(t) && cells <= (adjoint ? kWholeAdjoint : kWholeForward);
+}
+
+// One launch of four-column items (aligned sizes) is faster still, at every
+// count of shots: forward 1 shot 5.5 us a step, 16 shots 23.6, 32 shots 42;
+// adjoint (two-column items 7.6, 47.4 and 95.9) 6.7, 39.4 and 74. Past the cache
+// it is not (64 shots: forward 136 and adjoint 185 against 122 and 175 by tile
+// sets), so the shots of a larger call go through a stretch of steps (between
+// checkpoints) in groups whose fields fit: 64 shots in two groups 84 and 149.
+// Born steps hold two states and B' (32 shots: 138 in one group, 116 in two, 153
+// by tile sets). A shot larger than a group, or stretches too short to load a
+// group's fields for, go by tile sets.
+constexpr size_t kGroupCells = 13600000, kGroupCellsBorn = 6800000;
+constexpr int kGroupSteps = 8;
+enum class AcCall { kForward, kAdjoint, kBorn };
+void ac_set_path(sweep_plan* p, AcCall call) {
+  const size_t plane = (size_t)p->NX * p->NZ, cells = ac_cells(p);
+  const size_t most = call == AcCall::kBorn ? kGroupCellsBorn : kGroupCells;
+  p->wide = ac_default_tiling(p->tune) && ac_wide_sizes(p->NX, p->P, p->TZ) && plane <= most &&
+            (cells <= most || call == AcCall::kBorn || p->ckpt >= kGroupSteps);
+  p->whole = p->wide || ac_whole(p->tune, cells, call != AcCall::kForward);
+  const int ns = p->pb.nshots;
+  p->group = ns;
+  if (p->wide) {  // the fewest groups, of like size
+    const int fit = (int)(most / plane), n = (ns + fit - 1) / fit;
+    p->group = (ns + n - 1) / n;
+  }
+  p->g0 = 0;
+  p->gn = ns;
+}
+
+// Runs `body` (steps from rotation r) for each group of shots in turn.
+template <class F>
+int over_groups(sweep_plan* p, Rot& r, F body) {
+  const Rot r0 = r;
+  int rc = SWEEP_OK;
+  for (int g = 0; g < p->pb.nshots && !rc; g += p->group) {
+    p->g0 = g;
+    p->gn = std::min(p->group, p->pb.nshots - g);
+    r = r0;
+    rc = body();
+  }
+  p->g0 = 0;
+  p->gn = p->pb.nshots;
+  return rc;
+}
+
+// Step a of shots [s0, s0 + n) only.
+AcStep shot_window(AcStep a, int s0, int n) {
+  const size_t s = s0, plane = s * a.NX * a.NZ, xs = s * a.NZ * 2 * a.P, zs = s * a.NX * 2 * a.P;
+  auto move = [](auto*& ptr, size_t by) {
+    if (ptr) ptr += by;
+  };
+  a.nshots = n;
+  move(a.cur, plane);
+  move(a.prev, plane);
+  move(a.next, plane);
+  move(a.B_out, plane);
+  move(a.B_in, plane);
+  move(a.g, plane);
+  move(a.bB, plane);
+  move(a.psx_in, xs);
+  move(a.psx_out, xs);
+  move(a.zex_in, xs);
+  move(a.zex_out, xs);
+  move(a.psz_in, zs);
+  move(a.psz_out, zs);
+  move(a.zez_in, zs);
+  move(a.zez_out, zs);
+  move(a.src_cell, s * a.nsrc);
+  move(a.wavelet, s * a.nsrc * a.nt);
+  move(a.rec_off, s * a.ntiles);
+  move(a.gathers, s * a.nt * a.nrec);
+  move(a.resid, s * a.nt * a.nrec);
+  return a;
 }
 
 AcStep ac_base(const sweep_plan* p, void* work, const AcLayout& L) {
@@ -449,7 +524,8 @@ int ac_step(const sweep_plan* p, const AcStep& a, GridStep kind, hipStream_t s, 
            : kind == kGridFwd ? ac_launch_fwd(a, rz, prz, s, ev)
                               : ac_launch_born(a, rz, prz, s);
   if (ev && ev[4]) SWEEP_HIP(hipEventRecord(ev[4], s));
-  const int rc = ac_launch_grid(a, kind, s);
+  const int rc = p->wide ? ac_launch_wide(shot_window(a, p->g0, p->gn), kind, s)
+                         : ac_launch_grid(a, kind, s);
   if (rc) return rc;
   if (ev && ev[5]) SWEEP_HIP(hipEventRecord(ev[5], s));
   return SWEEP_OK;
@@ -543,23 +619,26 @@ int ac_forward_enqueue(sweep_plan* p, const float* model, const float* wavelet, 
       return rc;
     // steps of a stored segment also write B'^n (timed with the recomputation,
     // whose launches they are)
-    const int sg = n / k, m = n - sg * k;
+    const int sg = n / k, n0 = sg * k, n1 = save ? std::min(nt, n0 + k) : nt;
     const bool keepB = save && ac_kept(L, sg);
-    // a pair never spans a checkpoint (the state entering step n+1 is not formed)
-    if (two && n + 1 < nt && (!save || (n + 1) % k != 0)) {
-      if ((rc = ac_fwd_two(p, work, L, n, n % 2, gathers,
-                           keepB ? ac_bseg(p, work, L, sg, m) : nullptr,
-                           keepB ? ac_bseg(p, work, L, sg, m + 1) : nullptr, s, keepB)))
-        return rc;
-      n += 2;
-    } else {
-      if ((rc = keepB ? ac_fwd_one(p, work, L, n, n % 2, gathers, ac_bseg(p, work, L, sg, m), s,
-                                   kRecInt, kRecZ, kRecX)
-                      : ac_fwd_one(p, work, L, n, n % 2, gathers, nullptr, s, kFwdInt, kFwdZ,
-                                   kFwdX)))
-        return rc;
-      n += 1;
-    }
+    auto Bn = [&](int i) { return keepB ? ac_bseg(p, work, L, sg, i - n0) : nullptr; };
+    rc = over_groups(p, p->frot, [&]() {
+      int e = SWEEP_OK;
+      for (int i = n; i < n1 && !e;) {
+        // a pair never spans a checkpoint (the state entering step i+1 is not formed)
+        if (two && i + 1 < n1) {
+          e = ac_fwd_two(p, work, L, i, i % 2, gathers, Bn(i), Bn(i + 1), s, keepB);
+          i += 2;
+        } else {
+          e = keepB ? ac_fwd_one(p, work, L, i, i % 2, gathers, Bn(i), s, kRecInt, kRecZ, kRecX)
+                    : ac_fwd_one(p, work, L, i, i % 2, gathers, nullptr, s, kFwdInt, kFwdZ, kFwdX);
+          i += 1;
+        }
+      }
+      return e;
+    });
+    if (rc) return rc;
+    n = n1;
   }
   return SWEEP_OK;
 }
@@ -671,7 +750,6 @@ int ac_bwd_finish(sweep_plan* p, void* work, const AcLayout& L, float* grad, hip
 int ac_backward_enqueue(sweep_plan* p, const float* resid, float* grad, void* work,
                         const AcLayout& L, hipStream_t s) {
   const int nt = p->pb.nt, k = p->ckpt;
-  const size_t ns = p->pb.nshots;
   const bool two = ac_two_steps(p);
   int rc;
   if ((rc = ac_bwd_prologue(p, resid, work, L, s))) return rc;
@@ -679,28 +757,38 @@ int ac_backward_enqueue(sweep_plan* p, const float* resid, float* grad, void* wo
     const int n0 = sg * k, n1 = std::min(nt, n0 + k);
     // a stored segment was written by the forward: nothing to recompute
     if (!ac_kept(L, sg) && (rc = ac_bwd_restore(p, work, L, sg, s))) return rc;
-    for (int m = 0; m < n1 - n0 && !ac_kept(L, sg);) {
-      if (two && m + 1 < n1 - n0) {
-        if ((rc = ac_fwd_two(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m),
-                             ac_bseg(p, work, L, sg, m + 1), s, true)))
-          return rc;
-        m += 2;
-      } else {
-        if ((rc = ac_fwd_one(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m), s,
-                             kRecInt, kRecZ, kRecX)))
-          return rc;
-        m += 1;
-      }
+    if (!ac_kept(L, sg)) {
+      rc = over_groups(p, p->frot, [&]() {
+        int e = SWEEP_OK;
+        for (int m = 0; m < n1 - n0 && !e;) {
+          if (two && m + 1 < n1 - n0) {
+            e = ac_fwd_two(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m),
+                           ac_bseg(p, work, L, sg, m + 1), s, true);
+            m += 2;
+          } else {
+            e = ac_fwd_one(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m), s,
+                           kRecInt, kRecZ, kRecX);
+            m += 1;
+          }
+        }
+        return e;
+      });
+      if (rc) return rc;
     }
-    for (int n = n1 - 1; n >= n0;) {
-      if (two && n - 1 >= n0) {
-        if ((rc = ac_adj_two(p, work, L, resid, n, n0, n1, s))) return rc;
-        n -= 2;
-      } else {
-        if ((rc = ac_adj_one(p, work, L, resid, n, n0, n1, s))) return rc;
-        n -= 1;
+    rc = over_groups(p, p->arot, [&]() {
+      int e = SWEEP_OK;
+      for (int n = n1 - 1; n >= n0 && !e;) {
+        if (two && n - 1 >= n0) {
+          e = ac_adj_two(p, work, L, resid, n, n0, n1, s);
+          n -= 2;
+        } else {
+          e = ac_adj_one(p, work, L, resid, n, n0, n1, s);
+          n -= 1;
+        }
       }
-    }
+      return e;
+    });
+    if (rc) return rc;
     if ((rc = ac_bwd_fold(p, work, L, s))) return rc;
   }
   return ac_bwd_finish(p, work, L, grad, s);
@@ -754,7 +842,7 @@ int ac_forward(sweep_plan* p, const float* model, const float* wavelet, float* g
   int rc = check_work(p, save ? L.bwd_end : L.fwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  p->whole = ac_whole(p->tune, ac_cells(p), false);
+  ac_set_path(p, AcCall::kForward);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {model, wavelet, gathers, work, (const void*)(size_t)save};
   rc = run_maybe_graph(p->gfwd, graph, key, s, [&](hipStream_t st) {
@@ -780,7 +868,7 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  p->whole = ac_whole(p->tune, ac_cells(p), true);
+  ac_set_path(p, AcCall::kBorn);
   if ((rc = ac_fwd_prologue(p, model, wavelet, work, L, s))) return rc;
   const sweep_problem& pb = p->pb;
   const size_t ns = pb.nshots;
@@ -819,18 +907,24 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   // holds ckpt >= 2 of them); the perturbation takes single steps
   const bool two = ac_two_steps(p) && p->ckpt >= 2;
   float* Bn2 = Bn + ns * L.plane;
-  for (int n = 0; n < pb.nt;) {
-    if (two && n + 1 < pb.nt) {
-      if ((rc = ac_fwd_two(p, work, L, n, n % 2, nullptr, Bn, Bn2, s, false))) return rc;
-      if ((rc = dstep(n, Bn))) return rc;
-      if ((rc = dstep(n + 1, Bn2))) return rc;
-      n += 2;
-    } else {
-      if ((rc = ac_fwd_one(p, work, L, n, n % 2, nullptr, Bn, s, -1, -1, -1))) return rc;
-      if ((rc = dstep(n, Bn))) return rc;
-      n += 1;
+  rc = over_groups(p, p->frot, [&]() {
+    br = Rot();
+    int e = SWEEP_OK;
+    for (int n = 0; n < pb.nt && !e;) {
+      if (two && n + 1 < pb.nt) {
+        e = ac_fwd_two(p, work, L, n, n % 2, nullptr, Bn, Bn2, s, false);
+        if (!e) e = dstep(n, Bn);
+        if (!e) e = dstep(n + 1, Bn2);
+        n += 2;
+      } else {
+        e = ac_fwd_one(p, work, L, n, n % 2, nullptr, Bn, s, -1, -1, -1);
+        if (!e) e = dstep(n, Bn);
+        n += 1;
+      }
     }
-  }
+    return e;
+  });
+  if (rc) return rc;
   p->saved = false;
   return SWEEP_OK;
 }
@@ -846,7 +940,7 @@ int ac_backward(sweep_plan* p, const float* resid, float* grad, void* work, size
   ac_layout(p, L);
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
-  p->whole = ac_whole(p->tune, ac_cells(p), true);
+  ac_set_path(p, AcCall::kAdjoint);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {resid, grad, work};
   return run_maybe_graph(p->gbwd, graph, key, s, [&](hipStream_t st) {
@@ -916,13 +1010,18 @@ void batch_set_whole(sweep_batch* b, bool adjoint) {
   size_t cells = 0;
   for (const sweep_plan* p : b->plans) cells += ac_cells(p);
   b->whole = true;
-  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_whole(p->tune, cells, adjoint);
+  b->wide = cells <= kGroupCells;
+  for (const sweep_plan* p : b->plans) {
+    b->whole = b->whole && ac_whole(p->tune, cells, adjoint);
+    b->wide = b->wide && ac_default_tiling(p->tune) && ac_wide_sizes(p->NX, p->P, p->TZ);
+  }
+  b->whole = b->whole || b->wide;
   for (sweep_plan* p : b->plans) p->whole = b->whole;
 }
 int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep kind,
                hipStream_t s) {
   const int n = (int)steps.size();
-  if (b->whole) return ac_launch_grid_batch(steps.data(), n, kind, s);
+  if (b->whole) return ac_launch_grid_batch(steps.data(), n, kind, b->wide, s);
   return kind == kGridAdj ? ac_launch_adj_batch(steps.data(), n, b->rz, b->prz, s)
                           : ac_launch_fwd_batch(steps.data(), n, b->rz, b->prz, s);
 }
@@ -1800,7 +1899,7 @@ extern "C" int sweep_plan_autotune(sweep_plan* p, const float* d_model, const fl
       p->tune.pml_rz = cp;
       p->tune.tblock = tb;
       ac_build_tiling(p);
-      p->whole = ac_whole(p->tune, ac_cells(p), false);
+      ac_set_path(p, AcCall::kForward);
       // no deep tiles: same as tb = 1
       if (tb == 2 && !p->whole && !ac_two_steps(p)) continue;
       if ((rc = ac_upload_geometry(p, d_work, L, s))) break;
@@ -1809,15 +1908,19 @@ extern "C" int sweep_plan_autotune(sweep_plan* p, const float* d_model, const fl
         if (rc) break;
         SWEEP_HIP(hipEventRecord(e0, s));
         const bool two = ac_two_steps(p);
-        for (int n = 0; n < nsteps && !rc;) {
-          if (two && n + 1 < nsteps) {
-            rc = ac_fwd_two(p, d_work, L, n, n % 2, nullptr, nullptr, nullptr, s, false);
-            n += 2;
-          } else {
-            rc = ac_fwd_one(p, d_work, L, n, n % 2, nullptr, nullptr, s, kFwdInt, kFwdZ, kFwdX);
-            n += 1;
+        rc = over_groups(p, p->frot, [&]() {
+          int e = SWEEP_OK;
+          for (int n = 0; n < nsteps && !e;) {
+            if (two && n + 1 < nsteps) {
+              e = ac_fwd_two(p, d_work, L, n, n % 2, nullptr, nullptr, nullptr, s, false);
+              n += 2;
+            } else {
+              e = ac_fwd_one(p, d_work, L, n, n % 2, nullptr, nullptr, s, kFwdInt, kFwdZ, kFwdX);
+              n += 1;
+            }
           }
-        }
+          return e;
+        });
         SWEEP_HIP(hipEventRecord(e1, s));
         SWEEP_HIP(hipEventSynchronize(e1));
       }
