@@ -80,9 +80,6 @@ __device__ __forceinline__ f2 ld2(const float* f, unsigned i) {
 __device__ __forceinline__ void st4(float* f, unsigned i, f4 v) {
   *reinterpret_cast<f4u*>(reinterpret_cast<char*>(f) + i * 4u) = v;
 }
-__device__ __forceinline__ void st2(float* f, unsigned i, f2 v) {
-  *reinterpret_cast<f2u*>(reinterpret_cast<char*>(f) + i * 4u) = v;
-}
 // the same with the non-temporal hint
 __device__ __forceinline__ f4 ld4_nt(const float* f, unsigned i) {
   return __builtin_nontemporal_load(
@@ -165,10 +162,12 @@ __device__ __forceinline__ f4 dz_vz(const float* at, int st, f4 c, bool fs, int 
 // The tile of this work-group (1-D launch over tiles x shots) and this thread's
 // cells of it. kCols: what the right edge can cut. 4: NX is a multiple of 4, an
 // item of four columns (two in a column halo) is inside or outside as a whole.
-// 2, 1: NX is even, odd; tiles that lie inside the grid (kFull) still move four
-// columns at a time, at any 4-byte address, and the tiles at the right edge move
-// them in parts of kCols. Guarded loads come from a valid address and are
-// selected afterwards (no branch).
+// 2: it is not; tiles that lie inside the grid (kFull) move four columns at a time
+// all the same, at any 4-byte address, and so do those at the right edge, which
+// read the item there from further left and shift it (column by column, these tiles
+// set the time of a small launch: velocity, 459 x 245 cells, 11 shots, 16.7 us,
+// shifted 9.7). 1: NX < 4, columns one by one. Guarded loads come from a valid
+// address and are selected afterwards (no branch).
 template <int kCols, bool kFull>
 struct Tile {
   int NX, NZ, P, top, x0, z0;
@@ -203,12 +202,20 @@ struct Tile {
       const f4 v = ld4(f, ok ? (unsigned)(z * NX + x) : 0u);
       return f4{ok ? v.x : 0.0f, ok ? v.y : 0.0f, ok ? v.z : 0.0f, ok ? v.w : 0.0f};
     }
+    if (kCols == 2) {
+      const bool ok = q && zin(z) && xin(x);
+      const int xs = min(x, NX - 4), sh = ok ? x - xs : 4;
+      f4 v = ld4(f, ok ? (unsigned)(z * NX + xs) : 0u);
+      if (sh & 1) v = f4{v.y, v.z, v.w, 0.0f};
+      if (sh & 2) v = f4{v.z, v.w, 0.0f, 0.0f};
+      return sh & 4 ? kZ4 : v;
+    }
     const f2 a = part(f, z, x, q), b = part(f, z, x + 2, q);
     return f4{a.x, a.y, b.x, b.y};
   }
   // two columns, of a column halo too
   __device__ __forceinline__ f2 part(const float* f, int z, int x, bool q = true) const {
-    if (kCols >= 2) {
+    if (kCols == 4) {
       const bool ok = q && zin(z) && xin(x);
       const f2 v = ld2(f, ok ? (unsigned)(z * NX + x) : 0u);
       return f2{ok ? v.x : 0.0f, ok ? v.y : 0.0f};
@@ -234,16 +241,12 @@ struct Tile {
   __device__ __forceinline__ void put(float* f, f4 v) const {
     if (!zin(gz)) return;
     const unsigned k = (unsigned)(gz * NX + gx);
-    if (kCols == 4 || kFull) {
-      if (kFull || xin(gx)) st4(f, k, v);
-    } else if (kCols == 2) {
-      if (xin(gx)) st2(f, k, f2{v.x, v.y});
-      if (xin(gx + 2)) st2(f, k + 2, f2{v.z, v.w});
-    } else {
+    if (kFull || gx + 4 <= NX) {
+      st4(f, k, v);
+    } else if (kCols != 4) {
       if (xin(gx)) u32at(f, k) = v.x;
       if (xin(gx + 1)) u32at(f, k + 1) = v.y;
       if (xin(gx + 2)) u32at(f, k + 2) = v.z;
-      if (xin(gx + 3)) u32at(f, k + 3) = v.w;
     }
   }
   // a table along x, z (0 outside the grid)
@@ -1129,7 +1132,7 @@ int launch(const ElStep& a, bool adj, hipStream_t s, hipEvent_t* ev) {
   if (ev) SWEEP_HIP(hipEventRecord(ev[0], s));
   if (a.NX % 4 == 0)
     launch<4>(a, adj, s);
-  else if (a.NX % 2 == 0)
+  else if (a.NX >= 4)
     launch<2>(a, adj, s);
   else
     launch<1>(a, adj, s);
