@@ -733,9 +733,7 @@ def kernel_report(plan, w, kt):
     # Steps that take one launch for the whole grid are timed as the x frame; the
     # shots of aligned sizes go in groups whose fields fit the last-level cache.
     if all(v[0] == 0 for kk, v in kt.items() if not kk.endswith("_xpml")):
-        groups = 1
-        if NX % 4 == 0 and P % 4 == 0:
-            groups = -(-w.nshots // max(GROUP_CELLS // (NX * NZ), 1))
+        groups = -(-w.nshots // max(GROUP_CELLS // (NX * NZ), 1))
         for ph, b in base.items():
             per_launch[ph + "_xpml"] = ((b * NX * NZ + 16.0 * 2 * P * (NX + NZ)) *
                                         w.nshots / groups)

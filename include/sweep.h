@@ -102,9 +102,9 @@ typedef struct {
 
 /* Tile / launch choices (what the autotuner searches). Results are bitwise
  * independent of every field here. With the default tiling of an acoustic plan
- * (rz 8, pml_rz 4, tblock 2) a call over few cells takes one launch per step
- * for the whole grid in place of one per tile set; any other tiling is taken
- * as it is named. */
+ * (rz 8, pml_rz 4, tblock 2) a step takes one launch for the whole grid in place
+ * of one per tile set, the shots of a large call in groups; any other tiling is
+ * taken as it is named. */
 typedef struct {
   int rz;          /* acoustic tiles are 64 x 4 rz cells; rows per thread of the
                       interior kernel: 1, 2, 4 or 8 (default 8) */
@@ -287,7 +287,7 @@ int sweep_backward(sweep_plan* plan, const float* d_resid, float* d_grad, void* 
  * with tuning.tblock = 2 the two-step passes over the deep tiles are classes 9
  * (forward), 10 (adjoint) and 11 (recompute), and the interior classes then
  * time the remaining interior tiles. Steps that take one launch for the whole
- * grid are timed as x-frame launches. An elastic plan times each whole step
+ * grid are timed as x-frame launches (one for each group of shots). An elastic plan times each whole step
  * (both of its kernels) in classes 0, 3 and 6.
  * enable: 0 off; n >= 1 times the launches of every n-th step (n = 1: all); a
  * step pair of a two-step pass counts as three launch groups (deep pass, step

@@ -10,12 +10,18 @@
 // shared between the four cells, and those along z read 16 bytes of LDS a row.
 // Every thread stages its own cells; the halo rows are one item a thread (half of
 // the threads away from a z strip) and the side columns are left to one wave.
-// NX and P are multiples of 4, so an item is inside the grid, and inside a strip,
-// as a whole.
+// Where NX and P are multiples of 4, an item is inside the grid, and inside a strip,
+// as a whole. Other sizes take two-column items (acoustic_two.h) in the pieces near
+// an x strip or the right edge and four-column ones, at any 4-byte address, in the
+// others: 459 x 245 cells, 11 shots, 13.0 and 17.6 us a step (456 cells across: 9.0
+// and 12.9; by tile sets 23.8 and 29.8).
 //
 // The fields are read and written without the non-temporal hint: those of a few
 // dozen shots stay in the last-level cache from step to step. B' and the gradient
 // partials are used once a step and carry it.
+#include <algorithm>
+
+#include "acoustic_two.h"
 #include "fd.h"
 #include "internal.h"
 
@@ -23,17 +29,19 @@ namespace sweep {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+// rows start at any 4-byte address where NX is not a multiple of 4
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr f4 kZ4 = {0.0f, 0.0f, 0.0f, 0.0f};
 constexpr int kWZ = 16;  // rows of a piece
 static_assert(kThreads == kWZ * kTX / 4, "four cells per thread");
 
 // Four floats at element i of a work-group-uniform base (32-bit byte offset, as
 // u32at), plain and with the non-temporal hint.
-__device__ __forceinline__ const f4* at4(const float* f, unsigned i) {
-  return reinterpret_cast<const f4*>(reinterpret_cast<const char*>(f) + i * 4u);
+__device__ __forceinline__ const f4u* at4(const float* f, unsigned i) {
+  return reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(f) + i * 4u);
 }
-__device__ __forceinline__ f4* at4(float* f, unsigned i) {
-  return reinterpret_cast<f4*>(reinterpret_cast<char*>(f) + i * 4u);
+__device__ __forceinline__ f4u* at4(float* f, unsigned i) {
+  return reinterpret_cast<f4u*>(reinterpret_cast<char*>(f) + i * 4u);
 }
 __device__ __forceinline__ f4 lds4(const float* s) { return *reinterpret_cast<const f4*>(s); }
 __device__ __forceinline__ void put4(float* s, f4 v) { *reinterpret_cast<f4*>(s) = v; }
@@ -509,15 +517,45 @@ __device__ __forceinline__ void wide_adj(const AcStep& a, const Piece<kFull>& p,
   p.set(a.next + shot * plane, gz, gx, out);
 }
 
-template <GridStep kKind>
+// Pieces of a shot: tile columns [c0, c1) take 64 x 16 pieces of four-column
+// items, the others (none where NX and P are multiples of 4) 64 x 8 pieces of
+// two-column ones: those with a cell in or within 4 cells of an x strip or of the
+// grid's edge.
+struct Pieces {
+  int c0, c1, tiles_x, rows;  // rows: 16-row pieces along z
+  __host__ __device__ Pieces(const AcStep& a, bool aligned) {
+    tiles_x = a.tiles_x;
+    rows = a.ntiles / tiles_x * (a.tz / kWZ);
+    c0 = 0;
+    c1 = tiles_x;
+    if (aligned) return;
+    const int lo = a.P > 0 ? a.P + 4 : 4, hi = a.NX - lo;  // columns [lo, hi) are free of both
+    c0 = (lo + kTX - 1) / kTX;
+    c1 = hi / kTX;
+    // a few such columns are not worth the taller pieces, which a small grid waits
+    // for (170 x 97 cells, 3 shots: 1 column of 3, 6 % slower a gradient)
+    if (2 * (c1 - c0) < tiles_x) c0 = c1 = 0;
+  }
+  __host__ __device__ int four() const { return rows * (c1 - c0); }
+  __host__ __device__ int blocks() const { return four() + 2 * rows * (tiles_x - (c1 - c0)); }
+};
+
+template <GridStep kKind, int kUnit>
 __device__ __forceinline__ void wide_piece(const AcStep& a, int l, float* lds) {
-  const int nsub = a.tz / kWZ, per = a.ntiles * nsub;
-  const int shot = l / per, t = l - shot * per;
-  const int tile = t / nsub, row0 = (t - tile * nsub) * kWZ;
-  const int x0 = (tile % a.tiles_x) * kTX, z0 = (tile / a.tiles_x) * a.tz + row0;
+  const Pieces n(a, kUnit == 4);
+  const int per = n.blocks(), shot = l / per, t = l - shot * per, four = n.four();
   const int NX = a.NX, NZ = a.NZ, P = a.P;
+  if (kUnit != 4 && t >= four) {
+    const int w = n.tiles_x - (n.c1 - n.c0), u = t - four, row = u / w, c = u - row * w;
+    const int col = c < n.c0 ? c : c + (n.c1 - n.c0), z = row * two::kGZ, tz = z / a.tz;
+    two::piece<kKind, kUnit == 1>(a, shot, tz * n.tiles_x + col, col * kTX, z, z - tz * a.tz, lds);
+    return;
+  }
+  const int w = n.c1 - n.c0, row = t / w, col = n.c0 + t - row * w;
+  const int x0 = col * kTX, z0 = row * kWZ, tz = z0 / a.tz;
+  const int tile = tz * n.tiles_x + col, row0 = z0 - tz * a.tz;
   if (z0 >= NZ) return;
-  const bool hx = P > 0 && (x0 - 4 < P || x0 + kTX + 4 > NX - P);
+  const bool hx = kUnit == 4 && P > 0 && (x0 - 4 < P || x0 + kTX + 4 > NX - P);
   const bool hz = P > 0 && (z0 - 4 < P || z0 + kWZ + 4 > NZ - P);
   const bool full = x0 >= 4 && x0 + kTX + 4 <= NX && z0 >= 4 && z0 + kWZ + 4 <= NZ;
 #define SWEEP_PIECE(HX, HZ, FULL)                                               \
@@ -528,11 +566,17 @@ __device__ __forceinline__ void wide_piece(const AcStep& a, int l, float* lds) {
     else                                                                        \
       wide_fwd<HX, HZ, FULL, kKind == kGridBorn>(a, p, shot, tile, row0, lds);  \
   } while (0)
-  if (hx && hz)
-    SWEEP_PIECE(true, true, false);
-  else if (hx)
-    SWEEP_PIECE(true, false, false);
-  else if (hz)
+  if constexpr (kUnit == 4) {
+    if (hx && hz) {
+      SWEEP_PIECE(true, true, false);
+      return;
+    }
+    if (hx) {
+      SWEEP_PIECE(true, false, false);
+      return;
+    }
+  }
+  if (hz)
     SWEEP_PIECE(false, true, false);
   else if (full)
     SWEEP_PIECE(false, false, true);
@@ -541,54 +585,98 @@ __device__ __forceinline__ void wide_piece(const AcStep& a, int l, float* lds) {
 #undef SWEEP_PIECE
 }
 
+constexpr int lds_floats(GridStep kind, bool aligned) {
+  const int w = wide_lds(kind == kGridAdj), t = two::grid_lds(kind == kGridAdj);
+  return aligned || w > t ? w : t;
+}
+
 // 111 to 131 registers (the corner pieces) and 4 waves a SIMD: held to 96 for 5,
 // they spill and 32 shots take 50 and 78 us.
-template <GridStep kKind>
+template <GridStep kKind, int kUnit>
 __global__ __launch_bounds__(kThreads) void ac_wide_kernel(AcStep a) {
-  __shared__ __attribute__((aligned(16))) float lds[wide_lds(kKind == kGridAdj)];
-  wide_piece<kKind>(a, xcd_spread(blockIdx.x, gridDim.x), lds);
+  __shared__ __attribute__((aligned(16))) float lds[lds_floats(kKind, kUnit == 4)];
+  wide_piece<kKind, kUnit>(a, xcd_spread(blockIdx.x, gridDim.x), lds);
 }
 
-// Several plans in one launch (AcBatch).
-template <GridStep kKind>
+// Several plans in one launch (AcBatch); the least aligned one chooses the code.
+template <GridStep kKind, int kUnit>
 __global__ __launch_bounds__(kThreads) void ac_wide_batch_kernel(AcBatch b) {
-  __shared__ __attribute__((aligned(16))) float lds[wide_lds(kKind == kGridAdj)];
+  __shared__ __attribute__((aligned(16))) float lds[lds_floats(kKind, kUnit == 4)];
   int f = xcd_spread(blockIdx.x, gridDim.x), q = 0;
   while (q + 1 < b.nplans && f >= b.base[q + 1]) ++q;
-  wide_piece<kKind>(b.step[q], f - b.base[q], lds);
+  wide_piece<kKind, kUnit>(b.step[q], f - b.base[q], lds);
 }
 
-int wide_blocks(const AcStep& a) { return a.ntiles * (a.tz / kWZ) * a.nshots; }
+// what NX and P are multiples of: 4, 2 or 1
+int unit_of(const AcStep& a) { return (a.NX | a.P) & 1 ? 1 : (a.NX | a.P) & 2 ? 2 : 4; }
+int wide_blocks(const AcStep& a, bool aligned) { return Pieces(a, aligned).blocks() * a.nshots; }
 
-}  // namespace
+template <int kUnit>
+void launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
+  const dim3 g(wide_blocks(a, kUnit == 4)), t(kThreads);
+  switch (kind) {
+    case kGridFwd: hipLaunchKernelGGL((ac_wide_kernel<kGridFwd, kUnit>), g, t, 0, s, a); break;
+    case kGridAdj: hipLaunchKernelGGL((ac_wide_kernel<kGridAdj, kUnit>), g, t, 0, s, a); break;
+    default: hipLaunchKernelGGL((ac_wide_kernel<kGridBorn, kUnit>), g, t, 0, s, a); break;
+  }
+}
 
-bool ac_wide_sizes(int NX, int P, int tz) { return NX % 4 == 0 && P % 4 == 0 && tz % kWZ == 0; }
+template <int kUnit>
+void launch_wide_batch(const AcBatch& b, GridStep kind, hipStream_t s) {
+  const dim3 g(b.base[b.nplans]), t(kThreads);
+  if (kind == kGridAdj)
+    hipLaunchKernelGGL((ac_wide_batch_kernel<kGridAdj, kUnit>), g, t, 0, s, b);
+  else
+    hipLaunchKernelGGL((ac_wide_batch_kernel<kGridFwd, kUnit>), g, t, 0, s, b);
+}
 
-int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
-  if (!ac_wide_sizes(a.NX, a.P, a.tz)) {
-    set_error("one-launch step of four-column items: sizes not aligned");
+int check_wide(const AcStep& a, GridStep kind) {
+  if (a.tz % kWZ != 0) {
+    set_error("one-launch step: the tile height must be a multiple of 16");
     return SWEEP_EINVAL;
   }
   if (kind == kGridBorn && (!a.bdC || !a.bB)) {
     set_error("Born step without its perturbation operands");
     return SWEEP_EINVAL;
   }
-  const dim3 g(wide_blocks(a)), t(kThreads);
-  switch (kind) {
-    case kGridFwd: hipLaunchKernelGGL((ac_wide_kernel<kGridFwd>), g, t, 0, s, a); break;
-    case kGridAdj: hipLaunchKernelGGL((ac_wide_kernel<kGridAdj>), g, t, 0, s, a); break;
-    default: hipLaunchKernelGGL((ac_wide_kernel<kGridBorn>), g, t, 0, s, a); break;
+  return SWEEP_OK;
+}
+
+}  // namespace
+
+int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
+  const int rc = check_wide(a, kind);
+  if (rc) return rc;
+  switch (unit_of(a)) {
+    case 4: launch_wide<4>(a, kind, s); break;
+    case 2: launch_wide<2>(a, kind, s); break;
+    default: launch_wide<1>(a, kind, s);
   }
   SWEEP_HIP(hipGetLastError());
   return SWEEP_OK;
 }
 
-int ac_launch_wide_batch(const AcBatch& b, GridStep kind, hipStream_t s) {
-  const dim3 g(b.base[b.nplans]), t(kThreads);
-  if (kind == kGridAdj)
-    hipLaunchKernelGGL((ac_wide_batch_kernel<kGridAdj>), g, t, 0, s, b);
-  else
-    hipLaunchKernelGGL((ac_wide_batch_kernel<kGridFwd>), g, t, 0, s, b);
+int ac_launch_wide_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s) {
+  AcBatch b;
+  for (int q = 0; q < n;) {
+    b.nplans = 0;
+    b.base[0] = 0;
+    const int q0 = q;
+    int unit = 4;
+    for (; q < n && b.nplans < kPlansPerLaunch; ++q) {
+      const int rc = check_wide(steps[q], kind);
+      if (rc) return rc;
+      b.step[b.nplans++] = steps[q];
+      unit = std::min(unit, unit_of(steps[q]));
+    }
+    for (int k = 0; k < b.nplans; ++k)
+      b.base[k + 1] = b.base[k] + wide_blocks(steps[q0 + k], unit == 4);
+    switch (unit) {
+      case 4: launch_wide_batch<4>(b, kind, s); break;
+      case 2: launch_wide_batch<2>(b, kind, s); break;
+      default: launch_wide_batch<1>(b, kind, s);
+    }
+  }
   SWEEP_HIP(hipGetLastError());
   return SWEEP_OK;
 }

@@ -287,44 +287,30 @@ int check_work(const sweep_plan* p, size_t need, void* work, size_t bytes) {
 
 size_t ac_cells(const sweep_plan* p) { return (size_t)p->pb.nshots * p->NX * p->NZ; }
 
-// Whether the steps of a call over `cells` padded cells (all shots) take one
-// launch of two-column items for the whole grid; `adjoint`: the call has adjoint
-// or Born steps. Only under the default tiling, so that a tiling that the caller
-// names is the one that runs. One launch wins while launches and latency bound a
-// step, and beyond that while the fields stay in the 256 MB last-level cache. us
-// per step by tile sets / in one launch (1080 x 380 shots): forward 1 shot 21.3 /
-// 6.3, 16 shots (6.6 M cells) 37.2 / 29.9, 32 shots (13.1 M) 61.6 / 54.1, 64 shots
-// (26 M) 107.7 / 146.4; gradient 1 shot 70.9 / 21.7, 16 shots 140.3 / 114.2, 32
-// shots 238.2 / 239.4; Born 16 shots 87.5 / 69.7, 32 shots 153.0 / 159.8.
-constexpr size_t kWholeForward = 13600000, kWholeAdjoint = 8400000;
+// Whether the steps of a call take one launch for the whole grid, and the shots of
+// a group. Only under the default tiling, so that a tiling that the caller names is
+// the one that runs. One launch wins at every count of shots whose fields stay in
+// the 256 MB last-level cache; us per step of 1080 x 380 shots by tile sets / in one
+// launch: forward 1 shot 21.3 / 5.5, 16 shots (6.6 M cells) 37.2 / 23.6, 32 shots
+// (13.1 M) 65 / 42; adjoint 32 shots 95 / 74. Past the cache it does not (64 shots:
+// forward 122 / 136, adjoint 175 / 185), so the shots of a larger call go through a
+// stretch of steps (between checkpoints) in groups whose fields fit: 64 shots in two
+// groups 84 and 149. Born steps hold two states and B' (32 shots: 153 by tile sets,
+// 138 in one group, 116 in two). A shot larger than a group, or stretches too short
+// to load a group's fields for, go by tile sets.
+constexpr size_t kGroupCells = 13600000, kGroupCellsBorn = 6800000;
+constexpr int kGroupSteps = 8;
 bool ac_default_tiling(const sweep_tuning& t) {
   return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2;
 }
-bool ac_whole(const sweep_tuning& t, size_t cells, bool adjoint) {
-  return ac_default_tiling(t) && cells <= (adjoint ? kWholeAdjoint : kWholeForward);
-}
-
-// One launch of four-column items (aligned sizes) is faster still, at every
-// count of shots: forward 1 shot 5.5 us a step, 16 shots 23.6, 32 shots 42;
-// adjoint (two-column items 7.6, 47.4 and 95.9) 6.7, 39.4 and 74. Past the cache
-// it is not (64 shots: forward 136 and adjoint 185 against 122 and 175 by tile
-// sets), so the shots of a larger call go through a stretch of steps (between
-// checkpoints) in groups whose fields fit: 64 shots in two groups 84 and 149.
-// Born steps hold two states and B' (32 shots: 138 in one group, 116 in two, 153
-// by tile sets). A shot larger than a group, or stretches too short to load a
-// group's fields for, go by tile sets.
-constexpr size_t kGroupCells = 13600000, kGroupCellsBorn = 6800000;
-constexpr int kGroupSteps = 8;
-enum class AcCall { kForward, kAdjoint, kBorn };
-void ac_set_path(sweep_plan* p, AcCall call) {
+void ac_set_path(sweep_plan* p, bool born) {
   const size_t plane = (size_t)p->NX * p->NZ, cells = ac_cells(p);
-  const size_t most = call == AcCall::kBorn ? kGroupCellsBorn : kGroupCells;
-  p->wide = ac_default_tiling(p->tune) && ac_wide_sizes(p->NX, p->P, p->TZ) && plane <= most &&
-            (cells <= most || call == AcCall::kBorn || p->ckpt >= kGroupSteps);
-  p->whole = p->wide || ac_whole(p->tune, cells, call != AcCall::kForward);
+  const size_t most = born ? kGroupCellsBorn : kGroupCells;
+  p->whole = ac_default_tiling(p->tune) && plane <= most &&
+             (cells <= most || born || p->ckpt >= kGroupSteps);
   const int ns = p->pb.nshots;
   p->group = ns;
-  if (p->wide) {  // the fewest groups, of like size
+  if (p->whole) {  // the fewest groups, of like size
     const int fit = (int)(most / plane), n = (ns + fit - 1) / fit;
     p->group = (ns + n - 1) / n;
   }
@@ -524,8 +510,7 @@ int ac_step(const sweep_plan* p, const AcStep& a, GridStep kind, hipStream_t s, 
            : kind == kGridFwd ? ac_launch_fwd(a, rz, prz, s, ev)
                               : ac_launch_born(a, rz, prz, s);
   if (ev && ev[4]) SWEEP_HIP(hipEventRecord(ev[4], s));
-  const int rc = p->wide ? ac_launch_wide(shot_window(a, p->g0, p->gn), kind, s)
-                         : ac_launch_grid(a, kind, s);
+  const int rc = ac_launch_wide(shot_window(a, p->g0, p->gn), kind, s);
   if (rc) return rc;
   if (ev && ev[5]) SWEEP_HIP(hipEventRecord(ev[5], s));
   return SWEEP_OK;
@@ -608,11 +593,13 @@ float* ac_bseg(sweep_plan* p, void* work, const AcLayout& L, int sg, int m) {
   return at<float>(work, L.Bseg) + (size_t)m * ns * L.plane;
 }
 
+// nmax: stop after that many steps (the batch autotuner's short runs).
 int ac_forward_enqueue(sweep_plan* p, const float* model, const float* wavelet, float* gathers,
-                       void* work, const AcLayout& L, int save, hipStream_t s) {
+                       void* work, const AcLayout& L, int save, hipStream_t s,
+                       int nmax = INT_MAX) {
   int rc;
   if ((rc = ac_fwd_prologue(p, model, wavelet, work, L, s))) return rc;
-  const int nt = p->pb.nt, k = p->ckpt;
+  const int nt = std::min(p->pb.nt, nmax), k = p->ckpt;
   const bool two = ac_two_steps(p);
   for (int n = 0; n < nt;) {
     if (save && n % k == 0 && !ac_kept(L, n / k) && (rc = ac_checkpoint(p, work, L, n, s)))
@@ -747,48 +734,55 @@ int ac_bwd_finish(sweep_plan* p, void* work, const AcLayout& L, float* grad, hip
                           p->P, p->NX, scale, s);
 }
 
+// Steps [n0, n1) of segment sg: recomputation (from the restored state, unless its
+// B' is stored) and reverse sweep.
+int ac_segment_enqueue(sweep_plan* p, const float* resid, void* work, const AcLayout& L, int sg,
+                       int n0, int n1, hipStream_t s) {
+  const bool two = ac_two_steps(p);
+  int rc;
+  if (!ac_kept(L, sg)) {
+    rc = over_groups(p, p->frot, [&]() {
+      int e = SWEEP_OK;
+      for (int m = 0; m < n1 - n0 && !e;) {
+        if (two && m + 1 < n1 - n0) {
+          e = ac_fwd_two(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m),
+                         ac_bseg(p, work, L, sg, m + 1), s, true);
+          m += 2;
+        } else {
+          e = ac_fwd_one(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m), s,
+                         kRecInt, kRecZ, kRecX);
+          m += 1;
+        }
+      }
+      return e;
+    });
+    if (rc) return rc;
+  }
+  return over_groups(p, p->arot, [&]() {
+    int e = SWEEP_OK;
+    for (int n = n1 - 1; n >= n0 && !e;) {
+      if (two && n - 1 >= n0) {
+        e = ac_adj_two(p, work, L, resid, n, n0, n1, s);
+        n -= 2;
+      } else {
+        e = ac_adj_one(p, work, L, resid, n, n0, n1, s);
+        n -= 1;
+      }
+    }
+    return e;
+  });
+}
+
 int ac_backward_enqueue(sweep_plan* p, const float* resid, float* grad, void* work,
                         const AcLayout& L, hipStream_t s) {
   const int nt = p->pb.nt, k = p->ckpt;
-  const bool two = ac_two_steps(p);
   int rc;
   if ((rc = ac_bwd_prologue(p, resid, work, L, s))) return rc;
   for (int sg = L.nseg - 1; sg >= 0; --sg) {
     const int n0 = sg * k, n1 = std::min(nt, n0 + k);
     // a stored segment was written by the forward: nothing to recompute
     if (!ac_kept(L, sg) && (rc = ac_bwd_restore(p, work, L, sg, s))) return rc;
-    if (!ac_kept(L, sg)) {
-      rc = over_groups(p, p->frot, [&]() {
-        int e = SWEEP_OK;
-        for (int m = 0; m < n1 - n0 && !e;) {
-          if (two && m + 1 < n1 - n0) {
-            e = ac_fwd_two(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m),
-                           ac_bseg(p, work, L, sg, m + 1), s, true);
-            m += 2;
-          } else {
-            e = ac_fwd_one(p, work, L, n0 + m, m % 2, nullptr, ac_bseg(p, work, L, sg, m), s,
-                           kRecInt, kRecZ, kRecX);
-            m += 1;
-          }
-        }
-        return e;
-      });
-      if (rc) return rc;
-    }
-    rc = over_groups(p, p->arot, [&]() {
-      int e = SWEEP_OK;
-      for (int n = n1 - 1; n >= n0 && !e;) {
-        if (two && n - 1 >= n0) {
-          e = ac_adj_two(p, work, L, resid, n, n0, n1, s);
-          n -= 2;
-        } else {
-          e = ac_adj_one(p, work, L, resid, n, n0, n1, s);
-          n -= 1;
-        }
-      }
-      return e;
-    });
-    if (rc) return rc;
+    if ((rc = ac_segment_enqueue(p, resid, work, L, sg, n0, n1, s))) return rc;
     if ((rc = ac_bwd_fold(p, work, L, s))) return rc;
   }
   return ac_bwd_finish(p, work, L, grad, s);
@@ -842,7 +836,7 @@ int ac_forward(sweep_plan* p, const float* model, const float* wavelet, float* g
   int rc = check_work(p, save ? L.bwd_end : L.fwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  ac_set_path(p, AcCall::kForward);
+  ac_set_path(p, false);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {model, wavelet, gathers, work, (const void*)(size_t)save};
   rc = run_maybe_graph(p->gfwd, graph, key, s, [&](hipStream_t st) {
@@ -868,7 +862,7 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  ac_set_path(p, AcCall::kBorn);
+  ac_set_path(p, true);
   if ((rc = ac_fwd_prologue(p, model, wavelet, work, L, s))) return rc;
   const sweep_problem& pb = p->pb;
   const size_t ns = pb.nshots;
@@ -940,7 +934,7 @@ int ac_backward(sweep_plan* p, const float* resid, float* grad, void* work, size
   ac_layout(p, L);
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
-  ac_set_path(p, AcCall::kAdjoint);
+  ac_set_path(p, false);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {resid, grad, work};
   return run_maybe_graph(p->gbwd, graph, key, s, [&](hipStream_t st) {
@@ -1006,33 +1000,68 @@ AcStep adj_single_rot(sweep_plan* p, void* work, const AcLayout& L, const float*
 }
 
 // As for one plan, by the cells of all plans of the batch.
-void batch_set_whole(sweep_batch* b, bool adjoint) {
+void batch_set_whole(sweep_batch* b) {
   size_t cells = 0;
   for (const sweep_plan* p : b->plans) cells += ac_cells(p);
-  b->whole = true;
-  b->wide = cells <= kGroupCells;
-  for (const sweep_plan* p : b->plans) {
-    b->whole = b->whole && ac_whole(p->tune, cells, adjoint);
-    b->wide = b->wide && ac_default_tiling(p->tune) && ac_wide_sizes(p->NX, p->P, p->TZ);
-  }
-  b->whole = b->whole || b->wide;
+  b->whole = cells <= kGroupCells;
+  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_default_tiling(p->tune);
   for (sweep_plan* p : b->plans) p->whole = b->whole;
 }
 int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep kind,
                hipStream_t s) {
   const int n = (int)steps.size();
-  if (b->whole) return ac_launch_grid_batch(steps.data(), n, kind, b->wide, s);
+  if (b->whole) return ac_launch_wide_batch(steps.data(), n, kind, s);
   return kind == kGridAdj ? ac_launch_adj_batch(steps.data(), n, b->rz, b->prz, s)
                           : ac_launch_fwd_batch(steps.data(), n, b->rz, b->prz, s);
 }
-// nmax: stop after that many steps (the autotuner's short runs).
-int batch_forward_enqueue(sweep_batch* b, const float* const* models, const float* const* wavs,
+// Plans [lo, hi) of a batch that advance together. Under the default tiling these
+// are runs of consecutive plans whose fields fit the last-level cache together; a
+// plan that does not fit by itself goes alone, by groups of its shots. Otherwise,
+// all plans.
+struct BatchPart {
+  int lo, hi;
+};
+std::vector<BatchPart> batch_parts(const sweep_batch* b) {
+  const int np = (int)b->plans.size();
+  std::vector<BatchPart> parts;
+  size_t sum = 0;
+  for (int q = 0; q < np; ++q) {
+    sweep_plan* p = b->plans[q];
+    ac_set_path(p, false);
+    if (!p->whole) return {{0, np}};
+    const size_t cells = ac_cells(p);
+    if (parts.empty() || sum + cells > kGroupCells) {
+      parts.push_back({q, q});
+      sum = 0;
+    }
+    parts.back().hi = q + 1;
+    sum += cells;
+  }
+  return parts;
+}
+// The part as a batch of its own.
+struct SubBatch {
+  sweep_batch b;
+  std::vector<AcLayout> L;
+  std::vector<size_t> off;
+  SubBatch(const sweep_batch* all, const BatchPart& r, const std::vector<AcLayout>& la,
+           const std::vector<size_t>& oa)
+      : L(la.begin() + r.lo, la.begin() + r.hi), off(oa.begin() + r.lo, oa.begin() + r.hi) {
+    b.plans.assign(all->plans.begin() + r.lo, all->plans.begin() + r.hi);
+    b.device = all->device;
+    b.rz = all->rz;
+    b.prz = all->prz;
+  }
+};
+
+// One part of two or more plans (or all of them). nmax: stop after that many
+// steps (the autotuner's short runs).
+int batch_forward_part(sweep_batch* b, const float* const* models, const float* const* wavs,
                           float* const* gathers, void* work, const std::vector<AcLayout>& L,
-                          const std::vector<size_t>& off, int save, hipStream_t s,
-                          int nmax = INT_MAX) {
+                       const std::vector<size_t>& off, int save, hipStream_t s, int nmax) {
   const int np = (int)b->plans.size();
   int rc, maxnt = 0;
-  batch_set_whole(b, false);
+  batch_set_whole(b);
   for (int q = 0; q < np; ++q) {
     if ((rc = ac_fwd_prologue(b->plans[q], models[q], wavs[q], at<char>(work, off[q]), L[q], s)))
       return rc;
@@ -1080,16 +1109,37 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
   return SWEEP_OK;
 }
 
-// Recompute steps [n0, n1) of every plan (storing B^n) and reverse them, as
-// batched step pairs. resids[q] may be null (nothing injected: timing runs).
-int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work,
+int batch_forward_enqueue(sweep_batch* b, const float* const* models, const float* const* wavs,
+                          float* const* gathers, void* work, const std::vector<AcLayout>& L,
+                          const std::vector<size_t>& off, int save, hipStream_t s,
+                          int nmax = INT_MAX) {
+  int rc = SWEEP_OK;
+  for (const BatchPart& r : batch_parts(b)) {
+    const int q = r.lo;
+    if (r.hi - r.lo == 1) {
+      ac_set_path(b->plans[q], false);
+      rc = ac_forward_enqueue(b->plans[q], models[q], wavs[q], gathers[q], at<char>(work, off[q]),
+                              L[q], save, s, nmax);
+    } else {
+      SubBatch sub(b, r, L, off);
+      rc = batch_forward_part(&sub.b, models + q, wavs + q, gathers + q, work, sub.L, sub.off,
+                              save, s, nmax);
+    }
+    if (rc) return rc;
+  }
+  return rc;
+}
+
+// Recompute steps [n0, n1) of every plan of a part (storing B^n) and reverse them,
+// as batched step pairs. resids[q] may be null (nothing injected: timing runs).
+int batch_segment_part(sweep_batch* b, const float* const* resids, void* work,
                           const std::vector<AcLayout>& L, const std::vector<size_t>& off,
                           const std::vector<int>& n0, const std::vector<int>& n1, int lenmax,
                           hipStream_t s) {
   const int np = (int)b->plans.size();
   int rc;
   BatchPair B;
-  batch_set_whole(b, true);
+  batch_set_whole(b);
   // recompute the segments, storing B^n (not those the saving forward stored)
   for (int m = 0; m < lenmax; m += 2) {
     B.clear();
@@ -1147,6 +1197,32 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
   return SWEEP_OK;
 }
 
+int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work,
+                          const std::vector<AcLayout>& L, const std::vector<size_t>& off,
+                          const std::vector<int>& n0, const std::vector<int>& n1,
+                          hipStream_t s) {
+  int rc = SWEEP_OK;
+  for (const BatchPart& r : batch_parts(b)) {
+    const int q = r.lo;
+    if (r.hi - r.lo == 1) {
+      sweep_plan* p = b->plans[q];
+      if (n1[q] == n0[q]) continue;
+      ac_set_path(p, false);
+      rc = ac_segment_enqueue(p, resids[q], at<char>(work, off[q]), L[q], n0[q] / p->ckpt, n0[q],
+                              n1[q], s);
+    } else {
+      SubBatch sub(b, r, L, off);
+      const std::vector<int> m0(n0.begin() + r.lo, n0.begin() + r.hi),
+          m1(n1.begin() + r.lo, n1.begin() + r.hi);
+      int lenmax = 0;
+      for (size_t k = 0; k < m0.size(); ++k) lenmax = std::max(lenmax, m1[k] - m0[k]);
+      rc = batch_segment_part(&sub.b, resids + q, work, sub.L, sub.off, m0, m1, lenmax, s);
+    }
+    if (rc) return rc;
+  }
+  return rc;
+}
+
 int batch_backward_enqueue(sweep_batch* b, const float* const* resids, float* const* grads,
                            void* work, const std::vector<AcLayout>& L,
                            const std::vector<size_t>& off, hipStream_t s) {
@@ -1160,7 +1236,6 @@ int batch_backward_enqueue(sweep_batch* b, const float* const* resids, float* co
   std::vector<int> n0(np), n1(np);
   BatchPair B;
   for (int r = 0; r < maxseg; ++r) {
-    int lenmax = 0;
     for (int q = 0; q < np; ++q) {
       sweep_plan* p = b->plans[q];
       n0[q] = n1[q] = 0;
@@ -1168,11 +1243,10 @@ int batch_backward_enqueue(sweep_batch* b, const float* const* resids, float* co
       const int sg = L[q].nseg - 1 - r;
       n0[q] = sg * p->ckpt;
       n1[q] = std::min(p->pb.nt, n0[q] + p->ckpt);
-      lenmax = std::max(lenmax, n1[q] - n0[q]);
       if (!ac_kept(L[q], sg) && (rc = ac_bwd_restore(p, at<char>(work, off[q]), L[q], sg, s)))
         return rc;
     }
-    if ((rc = batch_segment_enqueue(b, resids, work, L, off, n0, n1, lenmax, s))) return rc;
+    if ((rc = batch_segment_enqueue(b, resids, work, L, off, n0, n1, s))) return rc;
     for (int q = 0; q < np; ++q)
       if (n1[q] > n0[q] && (rc = ac_bwd_fold(b->plans[q], at<char>(work, off[q]), L[q], s)))
         return rc;
@@ -1899,7 +1973,7 @@ extern "C" int sweep_plan_autotune(sweep_plan* p, const float* d_model, const fl
       p->tune.pml_rz = cp;
       p->tune.tblock = tb;
       ac_build_tiling(p);
-      ac_set_path(p, AcCall::kForward);
+      ac_set_path(p, false);
       // no deep tiles: same as tb = 1
       if (tb == 2 && !p->whole && !ac_two_steps(p)) continue;
       if ((rc = ac_upload_geometry(p, d_work, L, s))) break;
@@ -2041,8 +2115,9 @@ extern "C" int sweep_batch_autotune(sweep_batch* b, const float* const* d_models
       for (int tb = 1; tb <= 2 && !rc; ++tb) {
         if (cp > c) continue;
         if ((rc = apply(c, cp, tb))) break;
-        batch_set_whole(b, false);
-        bool deep = b->whole;
+        bool deep = batch_parts(b).size() > 1;
+        batch_set_whole(b);
+        deep = deep || b->whole;
         for (sweep_plan* p : b->plans) deep = deep || ac_two_steps(p);
         if (tb == 2 && !deep) continue;  // no deep tiles: the same as tblock = 1
         for (int q = 0; q < np && !rc; ++q)
@@ -2062,7 +2137,7 @@ extern "C" int sweep_batch_autotune(sweep_batch* b, const float* const* d_models
             if (!rc) rc = ac_bwd_restore(p, wq, L[q], 0, s);
           }
           if (!rc && for_backward)
-            rc = batch_segment_enqueue(b, noresid.data(), d_work, L, off, n0, n1, lenmax, s);
+            rc = batch_segment_enqueue(b, noresid.data(), d_work, L, off, n0, n1, s);
           if (!rc && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
             rc = SWEEP_EHIP;
         }

@@ -223,16 +223,11 @@ int ac_launch_inject_encoded(float* next, size_t plane, const int* src_cell, con
                              hipStream_t s);
 int ac_launch_born_prep(const float* v, const float* dv, float* dCs, int nx, int nz, int P,
                         double h, double dt, hipStream_t s);
-// One step of the whole grid in one launch, whatever the tile sets. Items of two
-// columns (acoustic_grid.hip; a.tz a multiple of 8), or of four where NX and P
-// are multiples of 4 and a.tz one of 16 (acoustic_wide.hip). A batch (`wide`: the
-// latter for all plans) has no Born steps.
+// One step of the whole grid in one launch, whatever the tile sets
+// (acoustic_wide.hip); a.tz must be a multiple of 16. A batch has no Born steps.
 enum GridStep { kGridFwd, kGridAdj, kGridBorn };
-int ac_launch_grid(const AcStep& a, GridStep kind, hipStream_t s);
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s);
-int ac_launch_grid_batch(const AcStep* steps, int n, GridStep kind, bool wide, hipStream_t s);
-bool ac_wide_sizes(int NX, int P, int tz);
-int ac_launch_wide_batch(const AcBatch& b, GridStep kind, hipStream_t s);  // of checked plans
+int ac_launch_wide_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s);
 int ac_launch_fwd_batch(const AcStep* steps, int n, int rz, int prz, hipStream_t s);
 // Two steps over the deep runs (a.drun): forward n and n+1, or adjoint n and n-1.
 int ac_launch_deep(const AcStep& a, bool adj, hipStream_t s, hipEvent_t* ev);

@@ -157,9 +157,8 @@ struct sweep_plan {
   // steps take one launch for the whole grid (set by every call, for the plan
   // alone or for the batch it runs in)
   bool whole = false;
-  // ... in items of four columns, the shots in groups of `group`, each advanced
-  // through a stretch of steps by itself; [g0, g0 + gn): the group being advanced
-  bool wide = false;
+  // ... the shots in groups of `group`, each advanced through a stretch of steps
+  // by itself; [g0, g0 + gn): the group being advanced
   int group = 0, g0 = 0, gn = 0;
   sweep::Rot frot, arot;  // forward / adjoint buffer rotation
   // elastic: receivers sorted by (shot, cell, r) for deterministic injection
@@ -226,7 +225,7 @@ struct sweep_batch {
   int device = -1;                 // the plans' device (-1: current at each call)
   int rz = 8, prz = 2;
   bool use_graph = false;
-  bool whole = false, wide = false;  // as in sweep_plan, for all plans (set by every call)
+  bool whole = false;  // as sweep_plan::whole, for all plans (set by every call)
   bool saved = false;
   const void* saved_work = nullptr;
   std::vector<unsigned> saved_gen;  // the plans' tuning generations at the saving forward
