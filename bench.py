@@ -441,9 +441,16 @@ VD_STEP_BYTES = {"fwd_int": 64, "rec_int": 80, "adj_int": 104}
 
 
 def el_step_kernels(torch, plan, grad, step_cells, step_bytes=EL_STEP_BYTES):
-    """Per-step kernel times of a staggered-grid plan (velocity + receivers +
-    stress, or the two reverse kernels and the residual injection), from one
-    more gradient timed every 10th step, with their algorithmic GB/s."""
+    """Per-step kernel times of a staggered-grid plan (velocity and stress with
+    the receivers, or the two reverse kernels with the residual injection), from
+    one more gradient timed every 10th launch pair, with their algorithmic GB/s.
+    The library's groups of shots (fields of up to 170 MiB) are timed one by one;
+    the times here are those of all the groups of a step."""
+    NX, NZ = plan.padded()
+    shots = step_cells // (NX * NZ)
+    fit = max((170 << 20) // ((16 if step_bytes is VD_STEP_BYTES else 20) * NX * NZ), 1)
+    groups = -(-shots // fit)
+    groups = -(-shots // -(-shots // groups))
     plan.set_profiling(True, 10)
     grad()
     torch.cuda.synchronize()
@@ -453,7 +460,7 @@ def el_step_kernels(torch, plan, grad, step_cells, step_bytes=EL_STEP_BYTES):
     for cls, nbytes in step_bytes.items():
         n, ms = kt.get(cls, (0, 0.0))
         if n:
-            us = 1e3 * ms / n
+            us = 1e3 * ms / n * groups
             out[cls] = {"steps_timed": n, "avg_us": round(us, 1), "bytes_per_cell": nbytes,
                         "algorithmic_GBps": round(nbytes * step_cells / us / 1e3, 1)}
     return out

@@ -287,8 +287,9 @@ int sweep_backward(sweep_plan* plan, const float* d_resid, float* d_grad, void* 
  * with tuning.tblock = 2 the two-step passes over the deep tiles are classes 9
  * (forward), 10 (adjoint) and 11 (recompute), and the interior classes then
  * time the remaining interior tiles. Steps that take one launch for the whole
- * grid are timed as x-frame launches (one for each group of shots). An elastic plan times each whole step
- * (both of its kernels) in classes 0, 3 and 6.
+ * grid are timed as x-frame launches (one for each group of shots). An elastic
+ * plan times each whole step (both of its kernels, of each group of shots) in
+ * classes 0, 3 and 6.
  * enable: 0 off; n >= 1 times the launches of every n-th step (n = 1: all); a
  * step pair of a two-step pass counts as three launch groups (deep pass, step
  * n, step n+1).

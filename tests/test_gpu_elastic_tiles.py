@@ -53,3 +53,29 @@ def test_tile_edges(orc, nx, nz, pml, nrec, fs, fluid):
     assert rel_l2(d.double().cpu().numpy(), dref) <= SEIS_TOL
     big = max(np.linalg.norm(b) for b in gref)
     assert max(np.linalg.norm(a - b) for a, b in zip(g, gref)) <= GRAD_TOL * big
+
+
+@pytest.mark.parametrize("fluid", [False, True])
+def test_groups_of_shots(fluid):
+    """Two groups of shots (23 of 520 x 1040 cells, fields of 249 or 199 MB) give
+    every shot's gathers and the sum of the shots' gradients that two calls of half
+    of the shots give: the gathers bit for bit, the gradients to float32 rounding
+    (their float64 sums over shots are rounded once or twice)."""
+    import paper_2604_14189_amd as sw
+    c = random_el_case(5, fs=0, nx=500, nz=1020, pml=10, nt=27, nshots=23, nrec=40, ckpt=9)
+    if fluid:
+        c.model[1] = 0.0
+    model = _dev(c.model[[0, 2]] if fluid else c.model)
+    outs = []
+    for lo, hi in ((0, 23), (0, 12), (12, 23)):
+        plan = sw.Plan(nx=c.nx, nz=c.nz, h=c.h, dt=c.dt, nt=c.nt, pml=c.pml, src_xz=c.src[lo:hi],
+                       rec_xz=c.rec[lo:hi], pml_vmax=c.vmax, pml_f0=c.f0, pml_R=c.R,
+                       ckpt_every=c.ckpt, physics=sw.ACOUSTIC_VD if fluid else sw.ELASTIC,
+                       free_surface=0)
+        d = plan.forward(model, _dev(c.wav[lo:hi]), save=True).clone()
+        outs.append((d, plan.backward(torch.cos(1e3 * d).contiguous()).double().clone()))
+    assert torch.equal(outs[0][0], torch.cat([outs[1][0], outs[2][0]]))
+    whole, parts = outs[0][1], outs[1][1] + outs[2][1]
+    eps, tiny = torch.finfo(torch.float32).eps, torch.finfo(torch.float32).tiny
+    scale = torch.abs(outs[1][1]) + torch.abs(outs[2][1]) + torch.abs(whole)
+    assert bool((torch.abs(whole - parts) <= eps * scale + tiny).all())
