@@ -107,10 +107,8 @@ struct Piece {
   __device__ __forceinline__ static f2 sel(bool ok0, bool ok1, f2 v, f2 u = kZero) {
     return f2{ok0 ? v.x : u.x, ok1 ? v.y : u.y};
   }
-  // f at row gz, columns gx and gx+1, 0 outside the grid (kFull: all inside)
-  template <bool kFull>
+  // f at row gz, columns gx and gx+1, 0 outside the grid
   __device__ __forceinline__ f2 get(const float* f, int gz, int gx) const {
-    if (kFull) return ld2(f, (unsigned)(gz * NX + gx));
     if (!kOdd) {
       const bool ok = in(gz, gx);
       return sel(ok, ok, ld2(f, ok ? (unsigned)(gz * NX + gx) : 0u));
@@ -121,10 +119,9 @@ struct Piece {
     const f2 v = ld2(f, ok0 || ok1 ? (unsigned)max(gz * NX + gx - sh, 0) : 0u);
     return sel(ok0, ok1, f2{sh ? v.y : v.x, v.y});
   }
-  template <bool kFull>
   __device__ __forceinline__ void set(float* f, int gz, int gx, f2 v) const {
     const unsigned i = (unsigned)(gz * NX + gx);
-    if (kFull || (in(gz, gx) && (!kOdd || gx + 1 < NX)))
+    if (in(gz, gx) && (!kOdd || gx + 1 < NX))
       st2(f, i, v);
     else if (kOdd && in(gz, gx))
       u32at(f, i) = v.x;
@@ -211,7 +208,7 @@ __device__ __forceinline__ int side_col(int q) {
   return q < G::hx / 2 ? 2 * q : kTX + 2 * q;
 }
 
-template <bool HX, bool HZ, bool kFull, bool kBorn, bool kOdd>
+template <bool HX, bool HZ, bool kBorn, bool kOdd>
 __device__ __forceinline__ void grid_fwd(const AcStep& a, const Piece<kOdd>& p, int shot,
                                          int tile, int row0, float* lds) {
   using G = GridGeom<HX, HZ>;
@@ -234,19 +231,19 @@ __device__ __forceinline__ void grid_fwd(const AcStep& a, const Piece<kOdd>& p, 
       const int c = a.src_cell[shot * a.nsrc + k];
       src = src || (c >= p.z0 * p.NX && c < (p.z0 + kGZ) * p.NX);
     }
-  const f2 own = p.template get<kFull>(cur, gz, gx);
+  const f2 own = p.get(cur, gz, gx);
   f2 zh[G::KZ], xh = kZero;
 #pragma unroll
   for (int k = 0; k < G::KZ; ++k)
-    zh[k] = p.template get<kFull>(cur, p.z0 - hz + halo_row<G>(zr + 8 * k), gx);
+    zh[k] = p.get(cur, p.z0 - hz + halo_row<G>(zr + 8 * k), gx);
   const int sr = tid / hx, sc = side_col<G>(tid % hx);
-  if (tid < G::NXF) xh = p.template get<kFull>(cur, p.z0 - hz + sr, p.x0 - hx + sc);
-  const f2 pp = p.template get<kFull>(a.prev + shot * plane, gz, gx);
-  const f2 cs = p.template get<kFull>(a.Cs, gz, gx);
+  if (tid < G::NXF) xh = p.get(cur, p.z0 - hz + sr, p.x0 - hx + sc);
+  const f2 pp = p.get(a.prev + shot * plane, gz, gx);
+  const f2 cs = p.get(a.Cs, gz, gx);
   f2 bd = kZero, bb = kZero;
   if constexpr (kBorn) {
-    bd = p.template get<kFull>(a.bdC, gz, gx);
-    bb = p.template get<kFull>(a.bB + shot * plane, gz, gx);
+    bd = p.get(a.bdC, gz, gx);
+    bb = p.get(a.bB + shot * plane, gz, gx);
   }
   // rings of the memory variables: columns x0-4 .. x0-1, x0+64 .. x0+67 of the
   // piece's rows (4 items a row, threads 0 .. 31) and rows z0-4 .. z0-1, z0+8 ..
@@ -345,8 +342,8 @@ __device__ __forceinline__ void grid_fwd(const AcStep& a, const Piece<kOdd>& p, 
       if (d == 0 && gx < p.NX) out.x += sw;
       if (d == 1 && gx + 1 < p.NX) out.y += sw;
     }
-  p.template set<kFull>(a.next + shot * plane, gz, gx, out);
-  if (a.B_out) p.template set<kFull>(a.B_out + shot * plane, gz, gx, B);
+  p.set(a.next + shot * plane, gz, gx, out);
+  if (a.B_out) p.set(a.B_out + shot * plane, gz, gx, B);
   if (e1 > e0) {  // the receivers of the tile in this piece's rows
     if constexpr (!(HX || HZ)) __syncthreads();  // sb is read until here
     put2(&sb[zr * kTX + lx], out);
@@ -360,7 +357,7 @@ __device__ __forceinline__ void grid_fwd(const AcStep& a, const Piece<kOdd>& p, 
   }
 }
 
-template <bool HX, bool HZ, bool kFull, bool kOdd>
+template <bool HX, bool HZ, bool kOdd>
 __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, int shot,
                                          int tile, int row0, float* lds) {
   using G = GridGeom<HX, HZ>;
@@ -378,16 +375,16 @@ __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, 
   const int* ro = a.rec_off + (size_t)shot * a.ntiles + tile;
   const int e0 = ro[0], e1 = a.resid && a.n >= 1 ? ro[1] : 0;
   const float* rs = a.resid + ((size_t)shot * a.nt + (a.n - 1)) * a.nrec;
-  const f2 l1 = p.template get<kFull>(cur, gz, gx);
-  const f2 cs = p.template get<kFull>(a.Cs, gz, gx);
+  const f2 l1 = p.get(cur, gz, gx);
+  const f2 cs = p.get(a.Cs, gz, gx);
   f2 zl[G::KZ], zc[G::KZ], zz[G::KZ], xl = kZero, xc = kZero, xz = kZero, xa = kZero;
   float za[G::KZ];
   int zq[G::KZ];
 #pragma unroll
   for (int k = 0; k < G::KZ; ++k) {
     const int hr = p.z0 - hz + halo_row<G>(zr + 8 * k);
-    zl[k] = p.template get<kFull>(cur, hr, gx);
-    zc[k] = p.template get<kFull>(a.Cs, hr, gx);
+    zl[k] = p.get(cur, hr, gx);
+    zc[k] = p.get(a.Cs, hr, gx);
     if constexpr (HZ) {
       zq[k] = p.zrow(hr);
       za[k] = p.zco(a.az, hr);
@@ -397,8 +394,8 @@ __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, 
   const int sr = tid / hx, sc = side_col<G>(tid % hx), sgx = p.x0 - hx + sc;
   bool s0 = false, s1 = false;
   if (tid < G::NXA) {
-    xl = p.template get<kFull>(cur, p.z0 + sr, sgx);
-    xc = p.template get<kFull>(a.Cs, p.z0 + sr, sgx);
+    xl = p.get(cur, p.z0 + sr, sgx);
+    xc = p.get(a.Cs, p.z0 + sr, sgx);
     if constexpr (HX) {
       s0 = p.xin(p.z0 + sr, sgx);
       s1 = kOdd ? p.xin(p.z0 + sr, sgx + 1) : s0;
@@ -437,10 +434,10 @@ __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, 
     ez = p.getz(a.zez_in + zso, row, gx);
     pzh = p.getz(a.psz_in + zso, rowh, gx);
   }
-  const f2 l2 = p.template get<kFull>(a.prev + shot * plane, gz, gx);
-  const f2 bb = p.template get<kFull>(a.B_in + shot * plane, gz, gx);
+  const f2 l2 = p.get(a.prev + shot * plane, gz, gx);
+  const f2 bb = p.get(a.B_in + shot * plane, gz, gx);
   f2 gg = kZero;
-  if (!a.g_init) gg = p.template get<kFull>(a.g + shot * plane, gz, gx);
+  if (!a.g_init) gg = p.get(a.g + shot * plane, gz, gx);
   int2 en = make_int2(0, 0);
   if (e0 + tid < e1) en = a.rec_ent[e0 + tid];
 
@@ -502,7 +499,7 @@ __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, 
   if constexpr (HX) out = out - XWin(&stx[zr * XW + 4 + lx], px).d1();
   if constexpr (HZ) out = out - ZWin(&stz[(zr + 4) * kTX + lx], kTX).d1();
   const f2 gb = l1 * bb;
-  p.template set<kFull>(a.g + shot * plane, gz, gx, a.g_init ? gb : gg + gb);
+  p.set(a.g + shot * plane, gz, gx, a.g_init ? gb : gg + gb);
   if (e1 > e0) {  // r_{n-1} at this piece's receivers; a cell's first entry adds all of them
     if constexpr (!(HX || HZ)) __syncthreads();  // sqx and sqz are read until here
     put2(&sqz[zr * kTX + lx], out);
@@ -519,7 +516,7 @@ __device__ __forceinline__ void grid_adj(const AcStep& a, const Piece<kOdd>& p, 
     __syncthreads();
     out = lds2(&sqz[zr * kTX + lx]);
   }
-  p.template set<kFull>(a.next + shot * plane, gz, gx, out);
+  p.set(a.next + shot * plane, gz, gx, out);
 }
 
 // The piece at columns x0, rows z0 of a shot: row0 its first row in the tile.
@@ -539,9 +536,9 @@ __device__ __forceinline__ void piece(const AcStep& a, int shot, int tile, int x
 #define SWEEP_PIECE(HX, HZ)                                                           \
   do {                                                                                \
     if constexpr (kKind == kGridAdj)                                                  \
-      grid_adj<HX, HZ, false>(a, p, shot, tile, row0, lds);                           \
+      grid_adj<HX, HZ>(a, p, shot, tile, row0, lds);                           \
     else                                                                              \
-      grid_fwd<HX, HZ, false, kKind == kGridBorn>(a, p, shot, tile, row0, lds);       \
+      grid_fwd<HX, HZ, kKind == kGridBorn>(a, p, shot, tile, row0, lds);       \
   } while (0)
   if (hx && hz)
     SWEEP_PIECE(true, true);
