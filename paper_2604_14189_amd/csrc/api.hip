@@ -1039,6 +1039,18 @@ std::vector<BatchPart> batch_parts(const sweep_batch* b) {
   }
   return parts;
 }
+// A plan that goes alone; a batch's launches are not timed by plan.
+struct LonePlan {
+  sweep_plan* p;
+  bool timing;
+  explicit LonePlan(sweep_plan* q) : p(q), timing(q->timer.on) {
+    p->timer.on = false;
+    ac_set_path(p, false);
+  }
+  ~LonePlan() { p->timer.on = timing; }
+  LonePlan(const LonePlan&) = delete;
+  LonePlan& operator=(const LonePlan&) = delete;
+};
 // The part as a batch of its own.
 struct SubBatch {
   sweep_batch b;
@@ -1117,7 +1129,7 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
   for (const BatchPart& r : batch_parts(b)) {
     const int q = r.lo;
     if (r.hi - r.lo == 1) {
-      ac_set_path(b->plans[q], false);
+      const LonePlan alone(b->plans[q]);
       rc = ac_forward_enqueue(b->plans[q], models[q], wavs[q], gathers[q], at<char>(work, off[q]),
                               L[q], save, s, nmax);
     } else {
@@ -1207,7 +1219,7 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
     if (r.hi - r.lo == 1) {
       sweep_plan* p = b->plans[q];
       if (n1[q] == n0[q]) continue;
-      ac_set_path(p, false);
+      const LonePlan alone(p);
       rc = ac_segment_enqueue(p, resids[q], at<char>(work, off[q]), L[q], n0[q] / p->ckpt, n0[q],
                               n1[q], s);
     } else {
