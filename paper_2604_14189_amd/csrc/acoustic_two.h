@@ -1,6 +1,6 @@
 // Acoustic step of a piece of 64 columns x 8 rows in items of two columns (the
 // recurrence of acoustic.hip with the same operations in the same order, so the
-// same bits), for any NX and P: the pieces that the four-column items of
+// same bits), for NX >= 2 and any P: the pieces that the four-column items of
 // acoustic_wide.hip do not fit. Device code.
 //
 // Such a step is bound by latency, of the chain load -> LDS -> memory variables ->
@@ -114,7 +114,8 @@ struct Piece {
       return sel(ok, ok, ld2(f, ok ? (unsigned)(gz * NX + gx) : 0u));
     }
     const bool ok0 = in(gz, gx), ok1 = in(gz, gx + 1);
-    // the item across the right edge is read one column further left
+    // the item across the right edge is read one column further left (there is one:
+    // NX >= 2)
     const int sh = ok0 && !ok1 ? 1 : 0;
     const f2 v = ld2(f, ok0 || ok1 ? (unsigned)max(gz * NX + gx - sh, 0) : 0u);
     return sel(ok0, ok1, f2{sh ? v.y : v.x, v.y});

@@ -635,6 +635,10 @@ int check_wide(const AcStep& a, GridStep kind) {
     set_error("one-launch step: the tile height must be a multiple of 16");
     return SWEEP_EINVAL;
   }
+  if (a.NX < 2) {
+    set_error("one-launch step: the grid must be two columns wide at least");
+    return SWEEP_EINVAL;
+  }
   if (kind == kGridBorn && (!a.bdC || !a.bB)) {
     set_error("Born step without its perturbation operands");
     return SWEEP_EINVAL;

@@ -303,10 +303,13 @@ constexpr int kGroupSteps = 8;
 bool ac_default_tiling(const sweep_tuning& t) {
   return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2;
 }
+// The one-launch kernels read two columns at a time: a grid of one column goes by
+// tile sets.
+bool ac_wide_takes(const sweep_plan* p) { return ac_default_tiling(p->tune) && p->NX > 1; }
 void ac_set_path(sweep_plan* p, bool born) {
   const size_t plane = (size_t)p->NX * p->NZ, cells = ac_cells(p);
   const size_t most = born ? kGroupCellsBorn : kGroupCells;
-  p->whole = ac_default_tiling(p->tune) && plane <= most &&
+  p->whole = ac_wide_takes(p) && plane <= most &&
              (cells <= most || born || p->ckpt >= kGroupSteps);
   const int ns = p->pb.nshots;
   p->group = ns;
@@ -1004,7 +1007,7 @@ void batch_set_whole(sweep_batch* b) {
   size_t cells = 0;
   for (const sweep_plan* p : b->plans) cells += ac_cells(p);
   b->whole = cells <= kGroupCells;
-  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_default_tiling(p->tune);
+  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_wide_takes(p);
   for (sweep_plan* p : b->plans) p->whole = b->whole;
 }
 int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep kind,

@@ -224,7 +224,8 @@ int ac_launch_inject_encoded(float* next, size_t plane, const int* src_cell, con
 int ac_launch_born_prep(const float* v, const float* dv, float* dCs, int nx, int nz, int P,
                         double h, double dt, hipStream_t s);
 // One step of the whole grid in one launch, whatever the tile sets
-// (acoustic_wide.hip); a.tz must be a multiple of 16. A batch has no Born steps.
+// (acoustic_wide.hip); a.tz must be a multiple of 16 and a.NX 2 or more. A batch has
+// no Born steps.
 enum GridStep { kGridFwd, kGridAdj, kGridBorn };
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s);
 int ac_launch_wide_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s);
