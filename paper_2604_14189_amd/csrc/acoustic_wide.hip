@@ -517,10 +517,20 @@ __device__ __forceinline__ void wide_adj(const AcStep& a, const Piece<kFull>& p,
   p.set(a.next + shot * plane, gz, gx, out);
 }
 
+// Tile columns [c0, c1) whose cells are all more than 4 cells from an x strip and
+// from the grid's edge.
+__host__ __device__ inline void free_columns(int NX, int P, int tiles_x, int& c0, int& c1) {
+  const int lo = P > 0 ? P + 4 : 4, hi = NX - lo;  // columns [lo, hi) are free of both
+  c0 = (lo + kTX - 1) / kTX;
+  c1 = hi / kTX;
+  // a few such columns are not worth the taller pieces, which a small grid waits
+  // for (170 x 97 cells, 3 shots: 1 column of 3, 6 % slower a gradient)
+  if (2 * (c1 - c0) < tiles_x) c0 = c1 = 0;
+}
+
 // Pieces of a shot: tile columns [c0, c1) take 64 x 16 pieces of four-column
 // items, the others (none where NX and P are multiples of 4) 64 x 8 pieces of
-// two-column ones: those with a cell in or within 4 cells of an x strip or of the
-// grid's edge.
+// two-column ones.
 struct Pieces {
   int c0, c1, tiles_x, rows;  // rows: 16-row pieces along z
   __host__ __device__ Pieces(const AcStep& a, bool aligned) {
@@ -528,13 +538,7 @@ struct Pieces {
     rows = a.ntiles / tiles_x * (a.tz / kWZ);
     c0 = 0;
     c1 = tiles_x;
-    if (aligned) return;
-    const int lo = a.P > 0 ? a.P + 4 : 4, hi = a.NX - lo;  // columns [lo, hi) are free of both
-    c0 = (lo + kTX - 1) / kTX;
-    c1 = hi / kTX;
-    // a few such columns are not worth the taller pieces, which a small grid waits
-    // for (170 x 97 cells, 3 shots: 1 column of 3, 6 % slower a gradient)
-    if (2 * (c1 - c0) < tiles_x) c0 = c1 = 0;
+    if (!aligned) free_columns(a.NX, a.P, tiles_x, c0, c1);
   }
   __host__ __device__ int four() const { return rows * (c1 - c0); }
   __host__ __device__ int blocks() const { return four() + 2 * rows * (tiles_x - (c1 - c0)); }
@@ -607,8 +611,6 @@ __global__ __launch_bounds__(kThreads) void ac_wide_batch_kernel(AcBatch b) {
   wide_piece<kKind, kUnit>(b.step[q], f - b.base[q], lds);
 }
 
-// what NX and P are multiples of: 4, 2 or 1
-int unit_of(const AcStep& a) { return (a.NX | a.P) & 1 ? 1 : (a.NX | a.P) & 2 ? 2 : 4; }
 int wide_blocks(const AcStep& a, bool aligned) { return Pieces(a, aligned).blocks() * a.nshots; }
 
 template <int kUnit>
@@ -648,10 +650,19 @@ int check_wide(const AcStep& a, GridStep kind) {
 
 }  // namespace
 
+int ac_wide_unit(int NX, int P) { return (NX | P) & 1 ? 1 : (NX | P) & 2 ? 2 : 4; }
+
+int ac_wide_two(int NX, int NZ, int P) {
+  const int tiles_x = (NX + kTX - 1) / kTX;
+  int c0, c1;
+  free_columns(NX, P, tiles_x, c0, c1);
+  return (NZ + two::kGZ - 1) / two::kGZ * (tiles_x - (c1 - c0));
+}
+
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
   const int rc = check_wide(a, kind);
   if (rc) return rc;
-  switch (unit_of(a)) {
+  switch (ac_wide_unit(a.NX, a.P)) {
     case 4: launch_wide<4>(a, kind, s); break;
     case 2: launch_wide<2>(a, kind, s); break;
     default: launch_wide<1>(a, kind, s);
@@ -671,7 +682,7 @@ int ac_launch_wide_batch(const AcStep* steps, int n, GridStep kind, hipStream_t 
       const int rc = check_wide(steps[q], kind);
       if (rc) return rc;
       b.step[b.nplans++] = steps[q];
-      unit = std::min(unit, unit_of(steps[q]));
+      unit = std::min(unit, ac_wide_unit(steps[q].NX, steps[q].P));
     }
     for (int k = 0; k < b.nplans; ++k)
       b.base[k + 1] = b.base[k] + wide_blocks(steps[q0 + k], unit == 4);

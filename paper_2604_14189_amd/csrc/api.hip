@@ -297,25 +297,64 @@ size_t ac_cells(const sweep_plan* p) { return (size_t)p->pb.nshots * p->NX * p->
 // stretch of steps (between checkpoints) in groups whose fields fit: 64 shots in two
 // groups 84 and 149. Born steps hold two states and B' (32 shots: 153 by tile sets,
 // 138 in one group, 116 in two). A shot larger than a group, or stretches too short
-// to load a group's fields for, go by tile sets.
+// to load a group's fields for, go by tile sets; so do many pieces of two-column
+// items (ac_two_pays).
 constexpr size_t kGroupCells = 13600000, kGroupCellsBorn = 6800000;
 constexpr int kGroupSteps = 8;
+enum class AcCall { kModel, kGradient, kBorn };
 bool ac_default_tiling(const sweep_tuning& t) {
   return t.rz == 8 && t.pml_rz == 4 && t.tblock == 2;
 }
 // The one-launch kernels read two columns at a time: a grid of one column goes by
 // tile sets.
 bool ac_wide_takes(const sweep_plan* p) { return ac_default_tiling(p->tune) && p->NX > 1; }
-void ac_set_path(sweep_plan* p, bool born) {
-  const size_t plane = (size_t)p->NX * p->NZ, cells = ac_cells(p);
-  const size_t most = born ? kGroupCellsBorn : kGroupCells;
-  p->whole = ac_wide_takes(p) && plane <= most &&
-             (cells <= most || born || p->ckpt >= kGroupSteps);
+bool ac_groups_fit(const sweep_plan* p, AcCall call) {
+  const size_t most = call == AcCall::kBorn ? kGroupCellsBorn : kGroupCells;
+  return ac_wide_takes(p) && (size_t)p->NX * p->NZ <= most &&
+         (ac_cells(p) <= most || call == AcCall::kBorn || p->ckpt >= kGroupSteps);
+}
+// Whether one launch pays where it has `two` pieces of two-column items (unit: what
+// the sizes are multiples of). On a full GPU such a piece takes 4.0 ns of a forward
+// step (unit 1) or 3.1 (unit 2) and a frame tile of the tile sets, which has the cells
+// of four, 11 to 12, so many of them lose what the fewer launches save: about 6 us a
+// step and tile set. Lines, with the time by tile sets over that in one launch on
+// both sides (80 to 6000 columns, 90 to 600 rows, 1 to 3000 shots):
+//   no interior tiles (the tile sets take one launch too), unit 1: 1250 (1000 to
+//     1300: 1.01 to 1.22, 1700 to 2500: 0.87 to 1.00), unit 2: 7000 (3500 to 5000:
+//     1.04 to 1.21, from 7000 on 0.87 to 1.10);
+//   otherwise unit 1: forward 7500 (5000 to 7000: 1.02 to 1.19, 7900 to 10000: 0.92 to
+//     1.05), gradient 8000 (5000 to 7000: 1.03 to 1.26, 8000 to 11600: 0.94 to 1.03,
+//     20000: 0.78 to 0.97), Born 10000 (5000 to 8500: 1.03 to 1.22), a batch 11000
+//     (10200 to 11000: 1.16 to 1.18, 19000: 0.94);
+//   unit 2: 10000 (7000 to 10000: 1.24 to 1.42, Born in groups from 11800 on 0.90 to
+//     1.02, 20000 and above: 0.86 to 1.10);
+//   a call in several groups of shots reads its fields from memory either way. In
+//     unit 1 its forward steps gain nothing (0.78 to 1.02), its Born steps up to 2500
+//     pieces (below 1000: 1.11 to 1.24, 2300 to 3700: 0.89 to 1.02, above: 0.84 to
+//     0.97), its gradients as above.
+bool ac_two_pays(size_t two, int unit, bool interior, bool split, bool batch, AcCall call) {
+  if (unit == 4) return true;
+  if (!interior) return two <= (unit == 1 ? 1250u : 7000u);
+  if (unit == 2) return two <= 10000u;
+  if (batch) return two <= 11000u;
+  switch (call) {
+    case AcCall::kModel: return !split && two <= 7500u;
+    case AcCall::kBorn: return two <= (split ? 2500u : 10000u);
+    default: return two <= 8000u;
+  }
+}
+void ac_set_path(sweep_plan* p, AcCall call) {
+  const size_t plane = (size_t)p->NX * p->NZ;
+  const size_t most = call == AcCall::kBorn ? kGroupCellsBorn : kGroupCells;
   const int ns = p->pb.nshots;
+  p->whole = ac_groups_fit(p, call);
   p->group = ns;
   if (p->whole) {  // the fewest groups, of like size
     const int fit = (int)(most / plane), n = (ns + fit - 1) / fit;
-    p->group = (ns + n - 1) / n;
+    const int group = (ns + n - 1) / n;
+    p->whole = ac_two_pays((size_t)group * ac_wide_two(p->NX, p->NZ, p->P),
+                           ac_wide_unit(p->NX, p->P), p->n_int > 0, n > 1, false, call);
+    if (p->whole) p->group = group;
   }
   p->g0 = 0;
   p->gn = ns;
@@ -839,7 +878,7 @@ int ac_forward(sweep_plan* p, const float* model, const float* wavelet, float* g
   int rc = check_work(p, save ? L.bwd_end : L.fwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  ac_set_path(p, false);
+  ac_set_path(p, save ? AcCall::kGradient : AcCall::kModel);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {model, wavelet, gathers, work, (const void*)(size_t)save};
   rc = run_maybe_graph(p->gfwd, graph, key, s, [&](hipStream_t st) {
@@ -865,7 +904,7 @@ int ac_born(sweep_plan* p, const float* model, const float* dmodel, const float*
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
   if ((rc = ac_upload_geometry(p, work, L, s))) return rc;
-  ac_set_path(p, true);
+  ac_set_path(p, AcCall::kBorn);
   if ((rc = ac_fwd_prologue(p, model, wavelet, work, L, s))) return rc;
   const sweep_problem& pb = p->pb;
   const size_t ns = pb.nshots;
@@ -937,7 +976,7 @@ int ac_backward(sweep_plan* p, const float* resid, float* grad, void* work, size
   ac_layout(p, L);
   int rc = check_work(p, L.bwd_end, work, bytes);
   if (rc) return rc;
-  ac_set_path(p, false);
+  ac_set_path(p, AcCall::kGradient);
   const bool graph = p->tune.use_graph && !p->timer.on;
   const std::vector<const void*> key = {resid, grad, work};
   return run_maybe_graph(p->gbwd, graph, key, s, [&](hipStream_t st) {
@@ -1002,14 +1041,6 @@ AcStep adj_single_rot(sweep_plan* p, void* work, const AcLayout& L, const float*
   return a;
 }
 
-// As for one plan, by the cells of all plans of the batch.
-void batch_set_whole(sweep_batch* b) {
-  size_t cells = 0;
-  for (const sweep_plan* p : b->plans) cells += ac_cells(p);
-  b->whole = cells <= kGroupCells;
-  for (const sweep_plan* p : b->plans) b->whole = b->whole && ac_wide_takes(p);
-  for (sweep_plan* p : b->plans) p->whole = b->whole;
-}
 int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep kind,
                hipStream_t s) {
   const int n = (int)steps.size();
@@ -1017,66 +1048,103 @@ int batch_step(const sweep_batch* b, const std::vector<AcStep>& steps, GridStep 
   return kind == kGridAdj ? ac_launch_adj_batch(steps.data(), n, b->rz, b->prz, s)
                           : ac_launch_fwd_batch(steps.data(), n, b->rz, b->prz, s);
 }
-// Plans [lo, hi) of a batch that advance together. Under the default tiling these
-// are runs of consecutive plans whose fields fit the last-level cache together; a
-// plan that does not fit by itself goes alone, by groups of its shots. Otherwise,
-// all plans.
+// Plans of a batch that advance together, whether a step of theirs takes one launch
+// for the whole grids. Under the default tiling one-launch parts are runs of
+// consecutive plans whose fields fit the last-level cache together, by the pieces of
+// all of them (the least aligned plan chooses the code); a plan that does not fit by
+// itself goes alone, by groups of its shots. The plans that one launch does not pay
+// for go together by tile sets, as do all plans of any other batch.
 struct BatchPart {
-  int lo, hi;
+  std::vector<int> q;
+  bool whole;
 };
-std::vector<BatchPart> batch_parts(const sweep_batch* b) {
-  const int np = (int)b->plans.size();
-  std::vector<BatchPart> parts;
-  size_t sum = 0;
-  for (int q = 0; q < np; ++q) {
-    sweep_plan* p = b->plans[q];
-    ac_set_path(p, false);
-    if (!p->whole) return {{0, np}};
-    const size_t cells = ac_cells(p);
-    if (parts.empty() || sum + cells > kGroupCells) {
-      parts.push_back({q, q});
-      sum = 0;
-    }
-    parts.back().hi = q + 1;
-    sum += cells;
+bool batch_pays(const sweep_batch* b, const std::vector<int>& run, AcCall call) {
+  size_t two = 0;
+  int unit = 4;
+  bool interior = false;
+  for (int q : run) {
+    const sweep_plan* p = b->plans[q];
+    two += (size_t)p->pb.nshots * ac_wide_two(p->NX, p->NZ, p->P);
+    unit = std::min(unit, ac_wide_unit(p->NX, p->P));
+    interior = interior || p->n_int > 0;
   }
+  return ac_two_pays(two, unit, interior, false, true, call);
+}
+std::vector<BatchPart> batch_parts(const sweep_batch* b, AcCall call) {
+  std::vector<int> all(b->plans.size());
+  for (size_t q = 0; q < all.size(); ++q) all[q] = (int)q;
+  std::vector<BatchPart> parts;
+  BatchPart run{{}, true}, rest{{}, false};
+  size_t sum = 0;
+  auto close = [&]() {
+    if (run.q.empty()) return;
+    bool pays = false;
+    if (run.q.size() == 1) {
+      ac_set_path(b->plans[run.q[0]], call);
+      pays = b->plans[run.q[0]]->whole;
+    } else {
+      pays = batch_pays(b, run.q, call);
+    }
+    if (pays)
+      parts.push_back(run);
+    else
+      rest.q.insert(rest.q.end(), run.q.begin(), run.q.end());
+    run.q.clear();
+    sum = 0;
+  };
+  for (int q : all) {
+    const sweep_plan* p = b->plans[q];
+    if (!ac_groups_fit(p, call)) return {{all, false}};
+    if (sum + ac_cells(p) > kGroupCells) close();
+    run.q.push_back(q);
+    sum += ac_cells(p);
+  }
+  close();
+  if (!rest.q.empty()) parts.push_back(rest);
   return parts;
 }
 // A plan that goes alone; a batch's launches are not timed by plan.
 struct LonePlan {
   sweep_plan* p;
   bool timing;
-  explicit LonePlan(sweep_plan* q) : p(q), timing(q->timer.on) {
+  LonePlan(sweep_plan* q, AcCall call) : p(q), timing(q->timer.on) {
     p->timer.on = false;
-    ac_set_path(p, false);
+    ac_set_path(p, call);
   }
   ~LonePlan() { p->timer.on = timing; }
   LonePlan(const LonePlan&) = delete;
   LonePlan& operator=(const LonePlan&) = delete;
 };
 // The part as a batch of its own.
+template <class T>
+std::vector<T> pick(const T* a, const std::vector<int>& q) {
+  std::vector<T> v;
+  for (int k : q) v.push_back(a[k]);
+  return v;
+}
 struct SubBatch {
   sweep_batch b;
   std::vector<AcLayout> L;
   std::vector<size_t> off;
   SubBatch(const sweep_batch* all, const BatchPart& r, const std::vector<AcLayout>& la,
            const std::vector<size_t>& oa)
-      : L(la.begin() + r.lo, la.begin() + r.hi), off(oa.begin() + r.lo, oa.begin() + r.hi) {
-    b.plans.assign(all->plans.begin() + r.lo, all->plans.begin() + r.hi);
+      : L(pick(la.data(), r.q)), off(pick(oa.data(), r.q)) {
+    b.plans = pick(all->plans.data(), r.q);
     b.device = all->device;
     b.rz = all->rz;
     b.prz = all->prz;
+    b.whole = r.whole;
+    for (sweep_plan* p : b.plans) p->whole = r.whole;
   }
 };
 
-// One part of two or more plans (or all of them). nmax: stop after that many
-// steps (the autotuner's short runs).
+// One part that advances together. nmax: stop after that many steps (the
+// autotuner's short runs).
 int batch_forward_part(sweep_batch* b, const float* const* models, const float* const* wavs,
                           float* const* gathers, void* work, const std::vector<AcLayout>& L,
                        const std::vector<size_t>& off, int save, hipStream_t s, int nmax) {
   const int np = (int)b->plans.size();
   int rc, maxnt = 0;
-  batch_set_whole(b);
   for (int q = 0; q < np; ++q) {
     if ((rc = ac_fwd_prologue(b->plans[q], models[q], wavs[q], at<char>(work, off[q]), L[q], s)))
       return rc;
@@ -1129,16 +1197,17 @@ int batch_forward_enqueue(sweep_batch* b, const float* const* models, const floa
                           const std::vector<size_t>& off, int save, hipStream_t s,
                           int nmax = INT_MAX) {
   int rc = SWEEP_OK;
-  for (const BatchPart& r : batch_parts(b)) {
-    const int q = r.lo;
-    if (r.hi - r.lo == 1) {
-      const LonePlan alone(b->plans[q]);
+  const AcCall call = save ? AcCall::kGradient : AcCall::kModel;
+  for (const BatchPart& r : batch_parts(b, call)) {
+    if (r.whole && r.q.size() == 1) {
+      const int q = r.q[0];
+      const LonePlan alone(b->plans[q], call);
       rc = ac_forward_enqueue(b->plans[q], models[q], wavs[q], gathers[q], at<char>(work, off[q]),
                               L[q], save, s, nmax);
     } else {
       SubBatch sub(b, r, L, off);
-      rc = batch_forward_part(&sub.b, models + q, wavs + q, gathers + q, work, sub.L, sub.off,
-                              save, s, nmax);
+      rc = batch_forward_part(&sub.b, pick(models, r.q).data(), pick(wavs, r.q).data(),
+                              pick(gathers, r.q).data(), work, sub.L, sub.off, save, s, nmax);
     }
     if (rc) return rc;
   }
@@ -1154,7 +1223,6 @@ int batch_segment_part(sweep_batch* b, const float* const* resids, void* work,
   const int np = (int)b->plans.size();
   int rc;
   BatchPair B;
-  batch_set_whole(b);
   // recompute the segments, storing B^n (not those the saving forward stored)
   for (int m = 0; m < lenmax; m += 2) {
     B.clear();
@@ -1217,21 +1285,21 @@ int batch_segment_enqueue(sweep_batch* b, const float* const* resids, void* work
                           const std::vector<int>& n0, const std::vector<int>& n1,
                           hipStream_t s) {
   int rc = SWEEP_OK;
-  for (const BatchPart& r : batch_parts(b)) {
-    const int q = r.lo;
-    if (r.hi - r.lo == 1) {
+  for (const BatchPart& r : batch_parts(b, AcCall::kGradient)) {
+    if (r.whole && r.q.size() == 1) {
+      const int q = r.q[0];
       sweep_plan* p = b->plans[q];
       if (n1[q] == n0[q]) continue;
-      const LonePlan alone(p);
+      const LonePlan alone(p, AcCall::kGradient);
       rc = ac_segment_enqueue(p, resids[q], at<char>(work, off[q]), L[q], n0[q] / p->ckpt, n0[q],
                               n1[q], s);
     } else {
       SubBatch sub(b, r, L, off);
-      const std::vector<int> m0(n0.begin() + r.lo, n0.begin() + r.hi),
-          m1(n1.begin() + r.lo, n1.begin() + r.hi);
+      const std::vector<int> m0 = pick(n0.data(), r.q), m1 = pick(n1.data(), r.q);
       int lenmax = 0;
       for (size_t k = 0; k < m0.size(); ++k) lenmax = std::max(lenmax, m1[k] - m0[k]);
-      rc = batch_segment_part(&sub.b, resids + q, work, sub.L, sub.off, m0, m1, lenmax, s);
+      rc = batch_segment_part(&sub.b, pick(resids, r.q).data(), work, sub.L, sub.off, m0, m1,
+                              lenmax, s);
     }
     if (rc) return rc;
   }
@@ -1988,7 +2056,7 @@ extern "C" int sweep_plan_autotune(sweep_plan* p, const float* d_model, const fl
       p->tune.pml_rz = cp;
       p->tune.tblock = tb;
       ac_build_tiling(p);
-      ac_set_path(p, false);
+      ac_set_path(p, AcCall::kModel);
       // no deep tiles: same as tb = 1
       if (tb == 2 && !p->whole && !ac_two_steps(p)) continue;
       if ((rc = ac_upload_geometry(p, d_work, L, s))) break;
@@ -2130,9 +2198,9 @@ extern "C" int sweep_batch_autotune(sweep_batch* b, const float* const* d_models
       for (int tb = 1; tb <= 2 && !rc; ++tb) {
         if (cp > c) continue;
         if ((rc = apply(c, cp, tb))) break;
-        bool deep = batch_parts(b).size() > 1;
-        batch_set_whole(b);
-        deep = deep || b->whole;
+        bool deep = false;
+        for (const BatchPart& r : batch_parts(b, AcCall::kModel)) deep = deep || r.whole;
+        for (sweep_plan* p : b->plans) p->whole = false;
         for (sweep_plan* p : b->plans) deep = deep || ac_two_steps(p);
         if (tb == 2 && !deep) continue;  // no deep tiles: the same as tblock = 1
         for (int q = 0; q < np && !rc; ++q)

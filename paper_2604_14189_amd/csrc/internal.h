@@ -228,6 +228,10 @@ int ac_launch_born_prep(const float* v, const float* dv, float* dCs, int nx, int
 // no Born steps.
 enum GridStep { kGridFwd, kGridAdj, kGridBorn };
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s);
+// What NX and P are multiples of (4, 2 or 1), which chooses the code of a one-launch
+// step, and the pieces of two-column items of a shot in the code of 2 and 1.
+int ac_wide_unit(int NX, int P);
+int ac_wide_two(int NX, int NZ, int P);
 int ac_launch_wide_batch(const AcStep* steps, int n, GridStep kind, hipStream_t s);
 int ac_launch_fwd_batch(const AcStep* steps, int n, int rz, int prz, hipStream_t s);
 // Two steps over the deep runs (a.drun): forward n and n+1, or adjoint n and n-1.

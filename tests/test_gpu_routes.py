@@ -4,6 +4,7 @@ tiling, tblock 1)."""
 import pytest
 import torch
 
+from synth import cases
 from tests.test_gpu_grid import _inputs, _run
 
 pytestmark = pytest.mark.gpu
@@ -36,5 +37,65 @@ def test_narrowest_grids_in_a_batch_bitwise():
     members = [_inputs(nx, nz, pml, 2, 1, seed=nx + nz)
                for nx, nz, pml in ((1, 40, 0), (60, 30, 10), (1, 3, 0), (1, 3, 7))]
     for m, (d, g) in zip(members, _batch(members)):
+        d1, g1 = _run(m, 1)[:2]
+        assert torch.equal(d, d1) and torch.equal(g, g1)
+
+
+def _one_launch(run, plan):
+    """Whether the steps of run(plan) took one launch for the whole grid (timed as
+    x-frame launches) and not one for each tile set."""
+    plan.set_profiling(True)
+    run(plan)
+    torch.cuda.synchronize()
+    n = {k: v[0] for k, v in plan.kernel_times().items()}
+    plan.set_profiling(False)
+    return sum(n.values()) == sum(v for k, v in n.items() if k.endswith("_xpml"))
+
+
+# sizes that are not multiples of 4 on both sides of the lines in pieces of
+# two-column items: 161 columns take 120 a shot on 320 rows, 162 (even) too
+@pytest.mark.parametrize("nx,nshots,forward,gradient", [
+    (141, 62, True, True), (141, 63, False, True), (141, 66, False, True),
+    (141, 67, False, False), (142, 83, True, True), (142, 84, False, False),
+    (144, 84, True, True)])
+def test_lines_of_unaligned_sizes(nx, nshots, forward, gradient):
+    """One launch or tile sets, and the bits of both with and without stored
+    segments (Born modelling, untimed, by its bits)."""
+    case = cases.random_case(3, nx=nx, nz=300, pml=10 if nx != 144 else 8, nt=8, nshots=nshots,
+                             nrec=9, ckpt=3)
+    v = torch.tensor(case.v, dtype=torch.float32, device="cuda")
+    wav = torch.tensor(case.wav, dtype=torch.float32, device="cuda")
+    r = torch.ones((case.nshots, case.nt, case.nrec), device="cuda")
+
+    def grad(plan):
+        plan.forward(v, wav, save=True)
+        plan.backward(r)
+    assert _one_launch(lambda p: p.forward(v, wav), case.plan()) == forward
+    assert _one_launch(grad, case.plan()) == gradient
+    ref = case.plan()
+    ref.set_tuning(tblock=1)
+    assert torch.equal(case.plan().forward(v, wav), ref.forward(v, wav))
+    for keep_b in (0, 1):
+        for a, b in zip(_run(case, 2, keep_b), _run(case, 1, keep_b)):
+            assert torch.equal(a, b)
+
+
+# narrow grids without interior tiles: 28 pieces a shot (line 1250 and 7000)
+@pytest.mark.parametrize("nx,nshots", [(101, 44), (101, 45), (102, 250), (102, 251)])
+def test_lines_of_narrow_sizes_bitwise(nx, nshots):
+    case = cases.random_case(4, nx=nx, nz=90, pml=10, nt=9, nshots=nshots, nrec=9, ckpt=4)
+    for a, b in zip(_run(case, 2), _run(case, 1)):
+        assert torch.equal(a, b)
+
+
+def test_batch_of_both_ways_bitwise():
+    """Plans that go by tile sets together (unaligned, many shots), one of them
+    between and one after plans that go alone in one launch."""
+    members = [cases.random_case(q, nx=nx, nz=nz, pml=P, nt=nt, nshots=ns, nrec=9, ckpt=9)
+               for q, (nx, nz, P, ns, nt) in enumerate([
+                   (101, 90, 10, 50, 20), (1000, 300, 40, 33, 14), (99, 80, 9, 60, 17),
+                   (1000, 300, 40, 33, 12), (87, 75, 10, 70, 23)])]
+    batch = _batch(members)
+    for m, (d, g) in zip(members, batch):
         d1, g1 = _run(m, 1)[:2]
         assert torch.equal(d, d1) and torch.equal(g, g1)
