@@ -234,14 +234,25 @@ ElStep step_base(const sweep_plan* p, void* work, const ElLayout& L, const ElCoe
 // checkpoints group by group, so that a group's fields (5 planes, 4 in a fluid) stay
 // in the 256 MB last-level cache. Variable density, 1080 x 380 cells, 64 shots (420
 // MB of fields), gradient of 100 steps: 133 ms all together, 101 ms in three groups.
-// Stretches too short to load a group's fields for are not split.
-constexpr size_t kGroupBytes = (size_t)170 << 20;
+// Stretches too short to load a group's fields for are not split. Nor are the shots
+// of a modelling call, which moves no traces or partials beside the fields, as long
+// as its fields and memory variables fit: split / whole, variable density 640 x 320
+// cells 180 MiB of fields (202 MB in all) 6.47 / 6.08 ms for 60 steps, 441 x 340 172
+// MiB (199 MB) 6.25 / 6.12, 191 MiB (221 MB) 6.85 / 7.14, elastic 640 x 320 181 MiB
+// (209 MB) 6.80 / 6.30, 441 x 340 181 MiB (221 MB) 7.41 / 7.72.
+constexpr size_t kGroupBytes = (size_t)170 << 20, kModelBytes = 212000000;
 constexpr int kGroupSteps = 8;
-int el_group(const sweep_plan* p) {
+int el_group(const sweep_plan* p, bool model) {
   const int ns = p->pb.nshots;
-  const size_t shot = (size_t)(p->pb.physics == SWEEP_ACOUSTIC_VD ? 16 : 20) * p->NX * p->NZ;
+  const bool fluid = p->pb.physics == SWEEP_ACOUSTIC_VD;
+  const size_t shot = (size_t)(fluid ? 16 : 20) * p->NX * p->NZ;
   const int fit = (int)std::min<size_t>(kGroupBytes / shot, ns);
   if (fit < 1 || p->ckpt < kGroupSteps) return ns;
+  if (model) {  // memory variables: two (four) along each axis, in its strips
+    const size_t rows = (p->pb.free_surface ? 1 : 2) * (size_t)p->P;
+    const size_t strips = (fluid ? 8 : 16) * (2 * (size_t)p->P * p->NZ + rows * p->NX);
+    if (ns * (shot + strips) <= kModelBytes) return ns;
+  }
   const int n = (ns + fit - 1) / fit;  // the fewest groups, of like size
   return (ns + n - 1) / n;
 }
@@ -333,7 +344,7 @@ int el_forward_enqueue(sweep_plan* p, const float* model, const float* wavelet, 
   base.gathers = gathers;
   const int k = p->ckpt;
   float* ck = at<float>(work, L.ck);
-  const int ng = el_group(p), nshots = pb.nshots;
+  const int ng = el_group(p, !save), nshots = pb.nshots;
   for (int n0 = 0; n0 < pb.nt;) {
     const int sg = n0 / k, n1 = save ? std::min(pb.nt, n0 + k) : pb.nt;
     if (save && !el_kept(L, sg))
@@ -430,7 +441,7 @@ int el_backward_enqueue(sweep_plan* p, const float* resid, float* grad, void* wo
   float* psbuf[2] = {adj + 5 * nsplane, adj + 13 * nsplane};
   for (int q = 0; q < kGradPlanes; ++q) abase.g[q] = gpart + q * nsplane;
 
-  const int ng = el_group(p), nshots = pb.nshots;
+  const int ng = el_group(p, false), nshots = pb.nshots;
   for (int sg = L.nseg - 1; sg >= 0; --sg) {
     const int n0 = sg * k, n1 = std::min(nt, n0 + k);
     // a stored segment's traces were written by the forward: nothing to recompute

@@ -99,3 +99,34 @@ def test_batch_of_both_ways_bitwise():
     for m, (d, g) in zip(members, batch):
         d1, g1 = _run(m, 1)[:2]
         assert torch.equal(d, d1) and torch.equal(g, g1)
+
+
+# staggered plans, 640 x 320 cells: a group holds the fields of 43 (fluid 54) shots, a
+# modelling call goes as one with the fields and memory variables of 47 (60)
+@pytest.mark.parametrize("fluid,nshots,groups", [
+    (False, 44, 2), (False, 48, 2), (False, 43, 1), (True, 57, 2), (True, 63, 2), (True, 54, 1)])
+def test_groups_of_staggered_calls(fluid, nshots, groups):
+    """Modelling calls are split into groups of shots only where their fields and
+    memory variables do not fit, saving calls where their fields do not; the gathers
+    are the same bits."""
+    import paper_2604_14189_amd as sw
+    c = cases.random_el_case(5, fs=1, nx=600, nz=300, pml=20, nt=9, nshots=nshots, nrec=9,
+                             ckpt=8)
+    model = torch.tensor(c.model[[0, 2]] if fluid else c.model, dtype=torch.float32, device="cuda")
+    wav = torch.tensor(c.wav, dtype=torch.float32, device="cuda")
+    plan = sw.Plan(nx=c.nx, nz=c.nz, h=c.h, dt=c.dt, nt=c.nt, pml=c.pml, src_xz=c.src,
+                   rec_xz=c.rec, pml_vmax=c.vmax, pml_f0=c.f0, pml_R=c.R, ckpt_every=c.ckpt,
+                   physics=sw.ACOUSTIC_VD if fluid else sw.ELASTIC, free_surface=1)
+
+    def steps(save):
+        plan.set_profiling(True)
+        d = plan.forward(model, wav, save=save).clone()
+        torch.cuda.synchronize()
+        n = plan.kernel_times()["fwd_int"][0]
+        plan.set_profiling(False)
+        return d, n
+    d0, n0 = steps(False)
+    d1, n1 = steps(True)
+    assert n1 == c.nt * groups
+    assert n0 == c.nt * (2 if nshots in (48, 63) else 1)
+    assert torch.equal(d0, d1)
