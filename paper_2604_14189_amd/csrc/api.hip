@@ -1317,7 +1317,6 @@ int batch_backward_enqueue(sweep_batch* b, const float* const* resids, float* co
     maxseg = std::max(maxseg, L[q].nseg);
   }
   std::vector<int> n0(np), n1(np);
-  BatchPair B;
   for (int r = 0; r < maxseg; ++r) {
     for (int q = 0; q < np; ++q) {
       sweep_plan* p = b->plans[q];
@@ -2174,11 +2173,9 @@ extern "C" int sweep_batch_autotune(sweep_batch* b, const float* const* d_models
   // segment) of every plan after the forward steps; the values are not used
   std::vector<int> n0(np, 0), n1(np, 0);
   std::vector<const float*> noresid(np, nullptr);
-  int lenmax = 0;
   for (int q = 0; q < np; ++q) {
-    sweep_plan* p = b->plans[q];
+    const sweep_plan* p = b->plans[q];
     n1[q] = std::min(std::min(steps, p->pb.nt), p->ckpt);
-    lenmax = std::max(lenmax, n1[q]);
   }
   std::vector<bool> timing(np);
   for (int q = 0; q < np; ++q) {
