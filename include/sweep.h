@@ -103,8 +103,8 @@ typedef struct {
 /* Tile / launch choices (what the autotuner searches). Results are bitwise
  * independent of every field here. With the default tiling of an acoustic plan
  * (rz 8, pml_rz 4, tblock 2) a step takes one launch for the whole grid in place
- * of one per tile set, the shots of a large call in groups; any other tiling is
- * taken as it is named. */
+ * of one per tile set wherever that was measured to pay, the shots of a large call
+ * in groups; any other tiling is taken as it is named. */
 typedef struct {
   int rz;          /* acoustic tiles are 64 x 4 rz cells; rows per thread of the
                       interior kernel: 1, 2, 4 or 8 (default 8) */
@@ -187,7 +187,9 @@ int sweep_plan_get_tuning(const sweep_plan* plan, sweep_tuning* t);
  *   {"arch":"gfx950","physics":"acoustic","mode":"plan-forward",
  *    "shapes":"NXxNZxNSHOTSxPML","rz":8,"pml_rz":4,"tblock":2,"us_per_step":...}
  * keyed by everything up to and including "shapes" (GPU arch, physics, mode,
- * padded NX and NZ, nshots, pad width), read first and appended to. Elastic,
+ * padded NX and NZ, nshots, pad width), read first and appended to. A line holds
+ * for the library that wrote it: after an update delete the file, or a tiling that
+ * was the fastest before is taken without a search. Elastic,
  * variable-density and VTI plans have no choice to make and return at once.
  * Synchronises `stream`. d_work needs the forward-only
  * workspace. Results never depend on the choice (bitwise). *chosen_rz (may be

@@ -14,11 +14,13 @@
 // as a whole. Other sizes take two-column items (acoustic_two.h) in the pieces near
 // an x strip or the right edge and four-column ones, at any 4-byte address, in the
 // others: 459 x 245 cells, 11 shots, 13.0 and 17.6 us a step (456 cells across: 9.0
-// and 12.9; by tile sets 23.8 and 29.8).
+// and 12.9; by tile sets 23.8 and 29.8). Calls with thousands of two-column pieces,
+// which keep a full GPU busier than the tile sets do, go by those (api.hip).
 //
 // The fields are read and written without the non-temporal hint: those of a few
 // dozen shots stay in the last-level cache from step to step. B' and the gradient
-// partials are used once a step and carry it.
+// partials are used once a step and carry it in the four-column pieces; the
+// two-column ones read and write them plainly.
 #include <algorithm>
 
 #include "acoustic_two.h"
@@ -594,8 +596,9 @@ constexpr int lds_floats(GridStep kind, bool aligned) {
   return aligned || w > t ? w : t;
 }
 
-// 111 to 131 registers (the corner pieces) and 4 waves a SIMD: held to 96 for 5,
-// they spill and 32 shots take 50 and 78 us.
+// The corner pieces set the registers: 124 forward and 112 in reverse, 4 waves a
+// SIMD, and 131 in a Born step, 3 waves. Held to 96 for 5 waves, forward and reverse
+// spill and 32 shots take 50 and 78 us.
 template <GridStep kKind, int kUnit>
 __global__ __launch_bounds__(kThreads) void ac_wide_kernel(AcStep a) {
   __shared__ __attribute__((aligned(16))) float lds[lds_floats(kKind, kUnit == 4)];

@@ -296,9 +296,12 @@ size_t ac_cells(const sweep_plan* p) { return (size_t)p->pb.nshots * p->NX * p->
 // forward 122 / 136, adjoint 175 / 185), so the shots of a larger call go through a
 // stretch of steps (between checkpoints) in groups whose fields fit: 64 shots in two
 // groups 84 and 149. Born steps hold two states and B' (32 shots: 153 by tile sets,
-// 138 in one group, 116 in two). A shot larger than a group, or stretches too short
-// to load a group's fields for, go by tile sets; so do many pieces of two-column
-// items (ac_two_pays).
+// 138 in one group, 116 in two). A shot larger than a group goes by tile sets, and so
+// do many pieces of two-column items (ac_two_pays). So does a call larger than a
+// group whose checkpoints are fewer than kGroupSteps steps apart (a modelling call
+// too, though its stretch is all of its steps): far on the safe side, since groups
+// gain from two steps on (64 shots of 1080 x 380, gradient of 48 steps, by tile sets /
+// in groups: checkpoints every 2 steps 25.1 / 23.7 ms, 4: 23.2 / 19.6, 8: 22.1 / 17.5).
 constexpr size_t kGroupCells = 13600000, kGroupCellsBorn = 6800000;
 constexpr int kGroupSteps = 8;
 enum class AcCall { kModel, kGradient, kBorn };

@@ -39,9 +39,11 @@ __device__ __forceinline__ float d1c(float p1, float m1, float p2, float m2, flo
   return fmaf(kB4, p4 - m4, s);
 }
 
-// Per-cell streams that a step touches exactly once (p^{n-1} in, p^{n+1} out,
-// B^n, the gradient partial) carry the non-temporal hint, so they do not evict
-// the halo lines that neighbouring tiles read again from L2.
+// Non-temporal accesses, for per-cell streams that a step touches exactly once, so
+// that they do not evict the halo lines that neighbouring tiles read again from L2:
+// B^n, traces and gradient partials, and in the acoustic tile sets (and VTI steps
+// whose fields exceed the last-level cache) p^{n-1} in and p^{n+1} out. Steps whose
+// fields stay in that cache read and write them without the hint.
 __device__ __forceinline__ float ld_nt(const float* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void st_nt(float* p, float v) { __builtin_nontemporal_store(v, p); }
 

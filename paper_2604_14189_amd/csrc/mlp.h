@@ -22,7 +22,8 @@ constexpr size_t kTh5 = 230400;
 constexpr size_t kThB5 = 230656;
 constexpr size_t kMlpParams = 230657;
 
-// bfloat16 weight pack: W1, W2..W4 [out][in], W2^T..W4^T [in][out], w5
+// bfloat16 weight pack: W1, W2..W4, W2^T..W4^T, each in the order in which its
+// products' matrix instructions read it (mlp_cast_kernel), then w5
 constexpr size_t kWp1 = 0;
 constexpr size_t kWpHidden[3] = {32768, 98304, 163840};
 constexpr size_t kWpHiddenT[3] = {229376, 294912, 360448};

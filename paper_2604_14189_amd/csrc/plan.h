@@ -155,14 +155,15 @@ struct sweep_plan {
   std::vector<int> ilist_all, ilist_ring, dlist;
   std::vector<int2> drun;  // deep tiles as chunks of tile-column runs
   // steps take one launch for the whole grid (set by every call, for the plan
-  // alone or for the batch it runs in)
+  // alone or for the part of a batch it runs in)
   bool whole = false;
   // ... the shots in groups of `group`, each advanced through a stretch of steps
   // by itself; [g0, g0 + gn): the group being advanced
   int group = 0, g0 = 0, gn = 0;
   sweep::Rot frot, arot;  // forward / adjoint buffer rotation
   // elastic: receivers sorted by (shot, cell, r) for deterministic injection
-  // (with a directory over tile rows), and the transposed z-taps of the first rows under a free surface
+  // (with a directory over tile rows), and the transposed z-taps of the first rows
+  // under a free surface
   std::vector<int4> rec_sorted;
   int tt_cnt[4][4];
   int tt_off[4][4][8];
@@ -225,7 +226,7 @@ struct sweep_batch {
   int device = -1;                 // the plans' device (-1: current at each call)
   int rz = 8, prz = 2;
   bool use_graph = false;
-  bool whole = false;  // as sweep_plan::whole, for all plans (set by every call)
+  bool whole = false;  // as sweep_plan::whole, for a part that runs as a batch
   bool saved = false;
   const void* saved_work = nullptr;
   std::vector<unsigned> saved_gen;  // the plans' tuning generations at the saving forward

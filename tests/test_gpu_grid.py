@@ -1,6 +1,6 @@
-"""Acoustic steps in one launch over the whole grid (the default tiling's path
-for calls over few cells) against the launches by tile set (a named tiling,
-tblock 1), bit for bit: the two do the same operations in the same order."""
+"""Acoustic steps in one launch over the whole grid (the path of the default
+tiling) against the launches by tile set (a named tiling, tblock 1), bit for bit:
+the two do the same operations in the same order."""
 import numpy as np
 import pytest
 import torch

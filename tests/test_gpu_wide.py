@@ -1,7 +1,7 @@
-"""Acoustic steps in one launch of four-column items (the default tiling's path
-for sizes that are of any size) against the launches by tile set (a named
-tiling, tblock 1), bit for bit: the two do the same operations in the same
-order. Grids smaller and larger than a 64 x 16 piece, ending at and next to its
+"""Acoustic steps in one launch, of four-column items and of two-column ones at
+the sides of sizes that are no multiples of 4 (the default tiling's path), against
+the launches by tile set (a named tiling, tblock 1), bit for bit: the two do the
+same operations in the same order. Grids smaller and larger than a 64 x 16 piece, ending at and next to its
 edges, with no pad and with one larger than the model; encoded shots; batches;
 and a call whose shots go through the steps in groups."""
 import pytest
