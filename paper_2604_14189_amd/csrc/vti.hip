@@ -844,8 +844,8 @@ bool vti_near_strip(int x0, int z0, int NX, int NZ, int P) {
 
 // The kernels hint their fields where P and G, old and new (32 bytes a cell),
 // exceed the last-level cache. 1080 x 380 cells, forward and reverse step, us:
-// 16 shots (210 MB) 115 and 185 with the hint, 101 and 180 without; 32 shots 212
-// and 350 with it, 223 and 364 without.
+// 16 shots (210 MB) 99 and 164 with the hint, 89 and 156 without; 20 shots (263 MB)
+// 116 and 198, 122 and 189; 32 shots 180 and 311, 195 and 327.
 static bool vti_hint(const VtiStep& a) {
   return (size_t)a.nshots * a.NX * a.NZ * 32 > (size_t)240 << 20;
 }
