@@ -219,7 +219,7 @@ struct Cells {
   }
 };
 
-template <bool HX, bool HZ, bool kFull, bool kBorn>
+template <bool HX, bool HZ, bool kFull, bool kBorn, bool kMany>
 __device__ __forceinline__ void wide_fwd(const AcStep& a, const Piece<kFull>& p, int shot,
                                          int tile, int row0, float* lds) {
   using G = WideGeom<HX, HZ>;
@@ -237,7 +237,10 @@ __device__ __forceinline__ void wide_fwd(const AcStep& a, const Piece<kFull>& p,
   const int* ro = a.rec_off + (size_t)shot * a.ntiles + tile;
   const int e0 = ro[0], e1 = a.gathers ? ro[1] : 0;
   bool src = false;  // a source in this piece's rows (work-group-uniform)
-  if constexpr (!kBorn)
+  int lsrc = -1;
+  if constexpr (kMany)
+    lsrc = lane_source(a, shot, 0);
+  else if constexpr (!kBorn)
     for (int k = 0; k < a.nsrc; ++k) {
       const int q = a.src_cell[shot * a.nsrc + k];
       src = src || (q >= p.z0 * p.NX && q < (p.z0 + kWZ) * p.NX);
@@ -335,7 +338,16 @@ __device__ __forceinline__ void wide_fwd(const AcStep& a, const Piece<kFull>& p,
   const f4 B = Bx + Bz;
   f4 out = fma4(cs, B, 2.0f * own - pp);
   if constexpr (kBorn) out = out + bd * bb;
-  if (src)  // in their order
+  if constexpr (kMany)
+    each_source(a, shot, lsrc, (p.z0 + (c.zr & ~3)) * p.NX, 4 * p.NX, [&](int cell, float sw) {
+      const int d = cell - (gz * p.NX + gx);
+      if ((unsigned)d < 4u && gx < p.NX) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (d == j) out[j] += sw;
+      }
+    });
+  if (src)
     for (int k = 0; k < a.nsrc; ++k) {
       const int d = a.src_cell[shot * a.nsrc + k] - (gz * p.NX + gx);
       const float sw = a.w * a.wavelet[((size_t)shot * a.nsrc + k) * a.nt + a.n];
@@ -570,7 +582,8 @@ __device__ __forceinline__ void wide_piece(const AcStep& a, int l, float* lds) {
     if constexpr (kKind == kGridAdj)                                            \
       wide_adj<HX, HZ, FULL>(a, p, shot, tile, row0, lds);                      \
     else                                                                        \
-      wide_fwd<HX, HZ, FULL, kKind == kGridBorn>(a, p, shot, tile, row0, lds);  \
+      wide_fwd<HX, HZ, FULL, kKind == kGridBorn, kKind == kGridEncoded>(        \
+          a, p, shot, tile, row0, lds);                                         \
   } while (0)
   if constexpr (kUnit == 4) {
     if (hx && hz) {
@@ -597,7 +610,7 @@ constexpr int lds_floats(GridStep kind, bool aligned) {
 }
 
 // The corner pieces set the registers: 124 forward and 112 in reverse, 4 waves a
-// SIMD, and 131 in a Born step, 3 waves. Held to 96 for 5 waves, forward and reverse
+// SIMD (127 with encoded shots), and 131 in a Born step, 3 waves. Held to 96 for 5 waves, forward and reverse
 // spill and 32 shots take 50 and 78 us.
 template <GridStep kKind, int kUnit>
 __global__ __launch_bounds__(kThreads) void ac_wide_kernel(AcStep a) {
@@ -622,6 +635,9 @@ void launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
   switch (kind) {
     case kGridFwd: hipLaunchKernelGGL((ac_wide_kernel<kGridFwd, kUnit>), g, t, 0, s, a); break;
     case kGridAdj: hipLaunchKernelGGL((ac_wide_kernel<kGridAdj, kUnit>), g, t, 0, s, a); break;
+    case kGridEncoded:
+      hipLaunchKernelGGL((ac_wide_kernel<kGridEncoded, kUnit>), g, t, 0, s, a);
+      break;
     default: hipLaunchKernelGGL((ac_wide_kernel<kGridBorn, kUnit>), g, t, 0, s, a); break;
   }
 }
@@ -665,6 +681,7 @@ int ac_wide_two(int NX, int NZ, int P) {
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s) {
   const int rc = check_wide(a, kind);
   if (rc) return rc;
+  if (kind == kGridFwd && a.nsrc > 1) kind = kGridEncoded;
   switch (ac_wide_unit(a.NX, a.P)) {
     case 4: launch_wide<4>(a, kind, s); break;
     case 2: launch_wide<2>(a, kind, s); break;

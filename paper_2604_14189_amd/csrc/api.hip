@@ -334,9 +334,26 @@ bool ac_groups_fit(const sweep_plan* p, AcCall call) {
 //   a call in several groups of shots reads its fields from memory either way. In
 //     unit 1 its forward steps gain nothing (0.78 to 1.02), its Born steps up to 2500
 //     pieces (below 1000: 1.11 to 1.24, 2300 to 3700: 0.89 to 1.02, above: 0.84 to
-//     0.97), its gradients as above.
-bool ac_two_pays(size_t two, int unit, bool interior, bool split, bool batch, AcCall call) {
+//     0.97), its gradients as above;
+//   encoded shots add their sources in a launch of its own by tile sets, a thread a
+//     shot, so more pieces pay the more sources there are. Unit 1, 2, 4, 8 and 32
+//     sources: without interior tiles 3000 (2800: 1.03 to 1.07, 4200: 0.93 to 0.98),
+//     4000 (4200: 0.96 to 1.02), 6000 (4200: 1.00 to 1.13, 6160: 0.98 to 1.05), 9000
+//     (8400: 1.02 to 1.19, 12600: 0.94 to 1.02); otherwise 10000 (9600: 1.00 to 1.05,
+//     10800: 0.98 to 0.99), 11000 (10800: 1.01 to 1.03, 13200: 0.95 to 0.96), 13000
+//     (13200: 1.00 to 1.10, 15600: 0.99 to 1.08), 20000 (19200: 1.03 to 1.14). Unit 2:
+//     20000 (19600: 1.07 to 1.12). In groups of shots as above up to 15 sources.
+bool ac_two_pays(size_t two, int unit, int nsrc, bool interior, bool split, bool batch,
+                 AcCall call) {
   if (unit == 4) return true;
+  if (nsrc > 1) {
+    const size_t some = 500 * (size_t)std::min(nsrc, 64);
+    if (!interior) return two <= (unit == 1 ? std::min<size_t>(2000 + some, 9000) : 20000);
+    if (unit == 2) return two <= 20000u;
+    if (split && nsrc < 16 && call == AcCall::kModel) return false;
+    if (split && nsrc < 16 && call == AcCall::kBorn) return two <= 2500u;
+    return two <= std::min<size_t>(9000 + some, 20000);
+  }
   if (!interior) return two <= (unit == 1 ? 1250u : 7000u);
   if (unit == 2) return two <= 10000u;
   if (batch) return two <= 11000u;
@@ -356,7 +373,7 @@ void ac_set_path(sweep_plan* p, AcCall call) {
     const int fit = (int)(most / plane), n = (ns + fit - 1) / fit;
     const int group = (ns + n - 1) / n;
     p->whole = ac_two_pays((size_t)group * ac_wide_two(p->NX, p->NZ, p->P),
-                           ac_wide_unit(p->NX, p->P), p->n_int > 0, n > 1, false, call);
+                           ac_wide_unit(p->NX, p->P), p->nsrc, p->n_int > 0, n > 1, false, call);
     if (p->whole) p->group = group;
   }
   p->g0 = 0;
@@ -1071,7 +1088,7 @@ bool batch_pays(const sweep_batch* b, const std::vector<int>& run, AcCall call) 
     unit = std::min(unit, ac_wide_unit(p->NX, p->P));
     interior = interior || p->n_int > 0;
   }
-  return ac_two_pays(two, unit, interior, false, true, call);
+  return ac_two_pays(two, unit, 1, interior, false, true, call);  // no encoded shots here
 }
 std::vector<BatchPart> batch_parts(const sweep_batch* b, AcCall call) {
   std::vector<int> all(b->plans.size());

@@ -226,7 +226,9 @@ int ac_launch_born_prep(const float* v, const float* dv, float* dCs, int nx, int
 // One step of the whole grid in one launch, whatever the tile sets
 // (acoustic_wide.hip); a.tz must be a multiple of 16 and a.NX 2 or more. A batch has
 // no Born steps.
-enum GridStep { kGridFwd, kGridAdj, kGridBorn };
+// kGridEncoded: the forward step's code for several sources per shot, which
+// ac_launch_wide chooses itself.
+enum GridStep { kGridFwd, kGridAdj, kGridBorn, kGridEncoded };
 int ac_launch_wide(const AcStep& a, GridStep kind, hipStream_t s);
 // What NX and P are multiples of (4, 2 or 1), which chooses the code of a one-launch
 // step, and the pieces of two-column items of a shot in the code of 2 and 1.

@@ -130,3 +130,29 @@ def test_groups_of_staggered_calls(fluid, nshots, groups):
     assert n1 == c.nt * groups
     assert n0 == c.nt * (2 if nshots in (48, 63) else 1)
     assert torch.equal(d0, d1)
+
+
+# encoded shots: fewer sources than lanes of a wave, one more, more than two waves
+# hold; widths and pads of every kind of piece
+@pytest.mark.parametrize("nsrc", [2, 64, 65, 130])
+@pytest.mark.parametrize("nx,nz,pml", [
+    (44, 28, 12), (45, 29, 10), (46, 27, 10), (300, 40, 10), (301, 17, 9), (5, 1, 3)])
+def test_many_sources_bitwise(nx, nz, pml, nsrc):
+    case = _inputs(nx, nz, pml, 2, nsrc, seed=nx + nz)
+    case.src[1, 0] = case.src[1, nsrc - 1]   # coincident, first and last
+    if nsrc > 64:
+        case.src[1, 63] = case.src[1, 64]
+    for a, b in zip(_run(case, 2), _run(case, 1)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("nsrc,nshots,forward", [(8, 108, True), (8, 109, False), (2, 83, True),
+                                                 (2, 84, False)])
+def test_lines_of_encoded_shots(nsrc, nshots, forward):
+    case = _inputs(141, 300, 10, nshots, nsrc, seed=3)
+    v = torch.tensor(case.v, dtype=torch.float32, device="cuda")
+    wav = torch.tensor(case.wav, dtype=torch.float32, device="cuda")
+    assert _one_launch(lambda p: p.forward(v, wav), case.plan()) == forward
+    ref = case.plan()
+    ref.set_tuning(tblock=1)
+    assert torch.equal(case.plan().forward(v, wav), ref.forward(v, wav))
