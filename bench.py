@@ -37,7 +37,7 @@ METRIC = "Gcell-updates/s fwd+adj; batched vs per-shot FWI gradient time at 1e-4
 # last-level cache serves. Keyed by kernel class and padded cells of a launch; valid
 # only while the kernel source hashes to the recorded value.
 TRAFFIC = {
-    ("adj_xpml", 32 * 1080 * 380): {"bytes_per_launch": 445917450, "source": "a077b724a546058d"},
+    ("adj_xpml", 32 * 1080 * 380): {"bytes_per_launch": 445883999, "source": "d1aff81a08f928a7"},
 }
 
 
