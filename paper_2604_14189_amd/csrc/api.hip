@@ -327,10 +327,10 @@ bool ac_groups_fit(const sweep_plan* p, AcCall call) {
 //     1.04 to 1.21, from 7000 on 0.87 to 1.10);
 //   otherwise unit 1: forward 7500 (5000 to 7000: 1.02 to 1.19, 7900 to 10000: 0.92 to
 //     1.05), gradient 8000 (5000 to 7000: 1.03 to 1.26, 8000 to 11600: 0.94 to 1.03,
-//     20000: 0.78 to 0.97), Born 10000 (5000 to 8500: 1.03 to 1.22), a batch 11000
-//     (10200 to 11000: 1.16 to 1.18, 19000: 0.94);
-//   unit 2: 10000 (7000 to 10000: 1.24 to 1.42, Born in groups from 11800 on 0.90 to
-//     1.02, 20000 and above: 0.86 to 1.10);
+//     20000: 0.78 to 0.97), Born 10000 (5000 to 8500: 1.03 to 1.22), a batch 12000
+//     (10200 to 11700: 1.16 to 1.18, 19000: 0.94);
+//   unit 2: 20000 (7000 to 10000: 1.24 to 1.42, 19900 to 20500: 0.97 to 1.13), in
+//     several groups 10000 (10200: 0.99 to 1.17, from 11800 on 0.85 to 1.04);
 //   a call in several groups of shots reads its fields from memory either way. In
 //     unit 1 its forward steps gain nothing (0.78 to 1.02), its Born steps up to 2500
 //     pieces (below 1000: 1.11 to 1.24, 2300 to 3700: 0.89 to 1.02, above: 0.84 to
@@ -355,8 +355,8 @@ bool ac_two_pays(size_t two, int unit, int nsrc, bool interior, bool split, bool
     return two <= std::min<size_t>(9000 + some, 20000);
   }
   if (!interior) return two <= (unit == 1 ? 1250u : 7000u);
-  if (unit == 2) return two <= 10000u;
-  if (batch) return two <= 11000u;
+  if (unit == 2) return two <= (split ? 10000u : 20000u);
+  if (batch) return two <= 12000u;
   switch (call) {
     case AcCall::kModel: return !split && two <= 7500u;
     case AcCall::kBorn: return two <= (split ? 2500u : 10000u);

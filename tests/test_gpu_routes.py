@@ -56,7 +56,7 @@ def _one_launch(run, plan):
 # two-column items: 161 columns take 120 a shot on 320 rows, 162 (even) too
 @pytest.mark.parametrize("nx,nshots,forward,gradient", [
     (141, 62, True, True), (141, 63, False, True), (141, 66, False, True),
-    (141, 67, False, False), (142, 83, True, True), (142, 84, False, False),
+    (141, 67, False, False), (142, 166, True, True), (142, 167, False, False),
     (144, 84, True, True)])
 def test_lines_of_unaligned_sizes(nx, nshots, forward, gradient):
     """One launch or tile sets, and the bits of both with and without stored
